@@ -201,7 +201,16 @@ int setup_network(Dev& d, DevMem& mem, const pa_eps_model_t* em, const double* t
     if ((rc = mem.alloc(&tvd, (size_t)T, "t_values"))) return rc;
     if ((rc = mem.alloc(&d.temb, (size_t)T * Hd, "temb"))) return rc;
     d.nsplit = mlp_splits(Hd);
-    if ((rc = mem.alloc(&d.Ep, (size_t)d.nsplit * ep_rows * Dz, "Ep"))) return rc;
+    // Ep holds the halves' partial outputs of every row. Partial outputs per 64 units take the
+    // same buffer for as many list entries as fit; a handle's own buffer grows by up to 8 MB for
+    // them, a workspace does not (what fits it stays as it was).
+    const size_t groups = (size_t)Hd / 64;
+    const size_t most = (size_t)mlp_fine_rows(Hd, d.ntok, d.mlp_grid);
+    size_t ep = (size_t)d.nsplit * ep_rows;
+    const size_t fine = most < ep_rows ? most : ep_rows;
+    if (!mem.ws && d.eps_mode && ep < fine * groups) ep = fine * groups;
+    d.fine_rows = (int32_t)(ep / groups < fine ? ep / groups : fine);
+    if ((rc = mem.alloc(&d.Ep, ep * Dz, "Ep"))) return rc;
     PA_HIP(hipMemcpyAsync(w1r, em->w1, (size_t)Hd * 16 * 2, hipMemcpyHostToDevice, st));
     PA_HIP(hipMemcpyAsync(w2r, em->w2, (size_t)Hd * Hd * 2, hipMemcpyHostToDevice, st));
     PA_HIP(hipMemcpyAsync(w3r, em->w3, (size_t)Hd * 16 * 2, hipMemcpyHostToDevice, st));

@@ -16,8 +16,9 @@
 //   3. eps^T = W3^T GELU(h2^T), MFMA fed straight from the GEMM2 accumulators (reduction
 //      index permuted to the accumulator layout; W3 stored pre-permuted);
 //   4. per-wave partials summed in a fixed order through LDS and unpatchified.
-// Two ways to finish (chosen per launch from the miss count, identically in every block,
-// by the time each takes):
+// Launches of few misses, whose 128-token items would leave most CUs idle, take smaller items
+// (fine_items). Two ways to finish the others (chosen per launch from the miss count, identically
+// in every block, by the time each takes):
 //   split outputs: each item is a work item of its own and writes its half's partial output;
 //      the Picard kernel adds the halves in a fixed order and writes the cache;
 //   whole outputs (at most two halves): one block runs both halves of a token block in turn,
@@ -51,7 +52,7 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
-constexpr int kTokMax = 128;            // tokens per work item (64 for single-latent launches)
+constexpr int kTokMax = 128;            // tokens per work item (fewer in launches of few misses)
 constexpr int kNH = 512;                // GEMM2 output units per work item
 constexpr int kKC = 256;                // h1 units per LDS buffer (K-chunk); two buffers
 constexpr int kWaves = 8;               // wave w owns output units [64w, 64w + 64) of the item
@@ -95,8 +96,8 @@ struct TokPos {
 };
 template <int kTok>
 __device__ __forceinline__ TokPos tok_pos(int e, int tb, int Himg, int Wimg) {
-    constexpr int kLog = kTok == 128 ? 7 : 6;
-    static_assert(kTok == (1 << kLog), "64 or 128 tokens per item");
+    constexpr int kLog = kTok == 128 ? 7 : (kTok == 64 ? 6 : 5);
+    static_assert(kTok == (1 << kLog), "32, 64 or 128 tokens per item");
     const int dw = e & 1, tl = (e >> 1) & (kTok - 1), dh = (e >> (kLog + 1)) & 1, c = e >> (kLog + 2);
     const int half_w = Wimg >> 1;
     const int tok = tb * kTok + tl;
@@ -110,8 +111,277 @@ __device__ __forceinline__ TokPos tok_pos(int e, int tb, int Himg, int Wimg) {
 
 }  // namespace
 
-// TOK: tokens per work item, 128, or 64 for launches of a single latent (twice the work items,
-// each half as long, where 128-token items would leave most CUs idle).
+// Position i of a half's K-chunk order: natural order for even halves; odd halves start with the
+// chunk a whole-output block still holds in buffer 0 (KCH - 2), then KCH - 1, KCH - 3, ..., 0.
+template <int KCH>
+__device__ __forceinline__ int korder(int odd, int i) {
+    return !odd ? i : (i == 0 ? KCH - 2 : (i == 1 ? KCH - 1 : KCH - 1 - i));
+}
+
+// Fine items, for launches whose 128-token items would leave most CUs without work: item =
+// (list entry, 32 TS tokens, UF output units). The block computes h1 of all H units of its tokens
+// into LDS once (KP = 2: half of K at a time), then GEMM2 from there; each wave owns 32 (UF < 512) or 64 output units, and its
+// W2^T fragments are in flight from before the gather. Every accumulation runs in the order of
+// the 128-token items (K-chunks, the 64 units of a GEMM3 chain, the waves of a half), so the
+// outputs are the same bits. UF = 512 covers a half and writes its split partial output; a
+// smaller UF writes one partial output per 64 units (a wave's share of a half) to
+// Ep[group][list entry], and the consumer adds them in the order the half's reduction takes.
+// Bound by one CU's stream of W2^T from L2 (UF x H x 2 bytes at ~46 B/clk: 2.2 us at UF = 128,
+// H = 1024) after its h1 GELUs (2.4 us per 32 tokens at H = 1024), hence few units and few tokens
+// per item while CUs are free. Launch time with 128-token items -> with these (1024 tokens,
+// H = 1024): 1 miss 34 -> 12 us, 2 misses 35 -> 15, 4 36 -> 20, 8 38 -> 28; 256 tokens, H = 512:
+// 16 misses 26 -> 11 us; 768 tokens, H = 2048: 1 miss 59 -> 27 us, 5 misses 67 -> 52.
+template <int H, int TS, int UF, int KP = 1>
+__device__ __forceinline__ void fine_items(const Dev& d, __bf16* h1, __bf16* xs, float* es, const int* mpre,
+                                           const int* fmiss, int fnewest) {
+    constexpr int NT = kWaves * 64, kTok = 32 * TS, HP = H / KP, HR = HP + 8, KS = H / 16, KCH = H / kKC, NUG = H / UF;
+    constexpr int UBW = UF == 512 ? 2 : 1;           // 32-unit blocks per wave
+    constexpr int UB = UF / 32;                      // 32-unit blocks per item
+    constexpr bool kSplitTok = UB == 4 && TS > 1;    // two wave groups, each half of the token slices
+    constexpr int SL = kSplitTok ? TS / 2 : TS;      // token slices per wave
+    constexpr int DEPTH = UBW == 2 ? 8 : 16;         // k-steps of W2^T fragments in flight
+    constexpr int KCP = KCH / KP;                    // K-chunks (and h1 unit blocks per wave) per pass
+    static_assert(UF == 128 || UF == 256 || UF == 512, "whole GEMM3 chains (64 units)");
+    static_assert(KS % DEPTH == 0 && 16 % DEPTH == 0, "a fragment group stays within a K-chunk");
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int g = lane >> 5, l32 = lane & 31;
+    const __amdgpu_buffer_rsrc_t w2r = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<__bf16*>(d.w2f), (short)0, H * H * 2, 0x00020000);
+    const f32x16 zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f,
+                           0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    const int nb = d.ntok / kTok, items = mpre[d.N] * nb * NUG;
+    const bool active = UB >= 8 || kSplitTok || w < UB;
+    const int sl0 = kSplitTok ? (w >> 2) * SL : 0;   // this wave's first token slice
+    for (int item = blockIdx.x; item < items; item += gridDim.x) {
+        // Unit groups fastest: with the blocks dealt to the XCDs in turn, an XCD's L2 fills with
+        // the W2 columns of few groups.
+        const int ug = item % NUG, tb = (item / NUG) % nb, gm = item / NUG / nb;
+        int n = 0;
+        while (mpre[n + 1] <= gm) ++n;               // sample of list entry gm (uniform)
+        const int jm = gm - mpre[n];
+        const Ctrl* ctrl = d.ctrl + n;
+        const int t = d.fused_slide ? fmiss[jm] : ctrl->miss_idx[jm];
+        const int newest = d.fused_slide ? fnewest : ctrl->newest;
+        const int ns = ug * UF / kNH, odd = ns & 1;
+        const int ub0 = ug * UB + (UB == 4 ? (w & 3) : w * UBW);   // this wave's first unit block
+
+        // ---- W2^T fragments of the first k-steps, then the gather: one round trip to memory
+        bf16x8 A[DEPTH][UBW];
+        auto load_a = [&](int i, int j) {            // k-step i of the half's order, into stage j
+            const int ks = korder<KCH>(odd, i / 16) * 16 + i % 16;
+#pragma unroll
+            for (int u = 0; u < UBW; ++u)
+                A[j][u] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(
+                    w2r, lane * 16, ((ub0 + u) * KS + ks) * 64 * 16, 0));
+        };
+        const float* xt = d.X + ((size_t)n * (d.T + 1) + min(t, newest)) * d.D;
+        const float* et = d.temb + (size_t)t * H;
+        constexpr int kPer = kTok * kFeat / NT, kEs = (H / 4 + NT - 1) / NT;
+        float xv[kPer];
+        float4 ev[kEs];
+        bf16x8 w1a[KCP];
+        auto load_w1 = [&](int ps) {                 // the wave's 32 units of each K-chunk of a pass
+#pragma unroll
+            for (int q = 0; q < KCP; ++q)
+                w1a[q] = *reinterpret_cast<const bf16x8*>(
+                    d.w1t + (size_t)(korder<KCH>(odd, ps * KCP + q) * kKC + w * 32 + l32) * kFeat + g * 8);
+        };
+#pragma unroll
+        for (int k = 0; k < kPer; ++k) xv[k] = xt[tok_pos<kTok>(tid + k * NT, tb, d.Himg, d.Wimg).idx];
+#pragma unroll
+        for (int k = 0; k < kEs; ++k)
+            if (tid + k * NT < H / 4) ev[k] = reinterpret_cast<const float4*>(et)[tid + k * NT];
+        load_w1(0);
+        if (active) {
+#pragma unroll
+            for (int j = 0; j < DEPTH; ++j) load_a(j, j);
+        }
+#pragma unroll
+        for (int k = 0; k < kPer; ++k) {
+            const TokPos p = tok_pos<kTok>(tid + k * NT, tb, d.Himg, d.Wimg);
+            xs[p.tl * kXRow + p.f] = (__bf16)xv[k];
+        }
+#pragma unroll
+        for (int k = 0; k < kEs; ++k)
+            if (tid + k * NT < H / 4) reinterpret_cast<float4*>(es)[tid + k * NT] = ev[k];
+        __syncthreads();
+
+        f32x16 acc[UBW][SL];
+#pragma unroll
+        for (int u = 0; u < UBW; ++u)
+#pragma unroll
+            for (int sl = 0; sl < SL; ++sl) acc[u][sl] = zero16;
+        const __bf16* hb = h1 + (sl0 * 32 + l32) * HR + g * 8;
+        // DEPTH k-steps from the pass's k-step p0 (i0 of the half's order); reloads the stages
+        // if more follow.
+        auto steps = [&](int i0, int p0, auto more_c) {
+#pragma unroll
+            for (int j = 0; j < DEPTH; ++j) {
+                bf16x8 B[SL];
+#pragma unroll
+                for (int sl = 0; sl < SL; ++sl)
+                    B[sl] = *reinterpret_cast<const bf16x8*>(hb + sl * 32 * HR + (p0 + j) * 16);
+#pragma unroll
+                for (int sl = 0; sl < SL; ++sl)
+#pragma unroll
+                    for (int u = 0; u < UBW; ++u) acc[u][sl] = mfma32(A[j][u], B[sl], acc[u][sl]);
+                if constexpr (decltype(more_c)::value) load_a(i0 + DEPTH + j, j);
+            }
+        };
+        constexpr int KSP = KS / KP;                 // k-steps per pass
+#pragma unroll
+        for (int ps = 0; ps < KP; ++ps) {
+            // ---- h1 of the pass's units: rows [token][units in the half's K order]
+#pragma unroll
+            for (int q = 0; q < KCP; ++q) {
+                const int u0 = korder<KCH>(odd, ps * KCP + q) * kKC + w * 32, p0 = q * kKC + w * 32;
+#pragma unroll
+                for (int sl = 0; sl < TS; ++sl) {
+                    const bf16x8 b = *reinterpret_cast<const bf16x8*>(xs + (sl * 32 + l32) * kXRow + g * 8);
+                    f32x16 c0;
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        const float4 e4 = *reinterpret_cast<const float4*>(es + u0 + g * 4 + r * 8);
+                        c0[r * 4 + 0] = e4.x;
+                        c0[r * 4 + 1] = e4.y;
+                        c0[r * 4 + 2] = e4.z;
+                        c0[r * 4 + 3] = e4.w;
+                    }
+                    c0 = mfma32(w1a[q], b, c0);
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        bf16x4 v;
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) v[i] = (__bf16)gelu2_erf(c0[r * 4 + i]);
+                        *reinterpret_cast<bf16x4*>(h1 + (sl * 32 + l32) * HR + p0 + r * 8 + g * 4) = v;
+                    }
+                }
+            }
+            if (ps + 1 < KP) load_w1(ps + 1);
+            __syncthreads();
+            // ---- GEMM2 over them
+            if (active) {
+                for (int i = 0; i + DEPTH < KSP; i += DEPTH) steps(ps * KSP + i, i, std::true_type{});
+                if (ps + 1 < KP) steps((ps + 1) * KSP - DEPTH, KSP - DEPTH, std::true_type{});
+                else steps(KS - DEPTH, KSP - DEPTH, std::false_type{});
+            }
+            if (ps + 1 < KP) __syncthreads();        // the pass's h1 is read before the next one's
+        }
+
+        // ---- GEMM3: chains of 64 units (two unit blocks) per token slice
+        f32x16 acc3[SL];
+        auto gemm3 = [&](int u) {
+#pragma unroll
+            for (int jj = 0; jj < 2; ++jj) {
+                const bf16x8 a3 = *reinterpret_cast<const bf16x8*>(
+                    d.w3p + (((size_t)(ub0 + u) * 2 + jj) * 64 + lane) * 8);
+#pragma unroll
+                for (int sl = 0; sl < SL; ++sl) {
+                    bf16x8 b3;
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) b3[i] = (__bf16)gelu2_erf(acc[u][sl][jj * 8 + i]);
+                    acc3[sl] = mfma32(a3, b3, acc3[sl]);
+                }
+            }
+        };
+#pragma unroll
+        for (int sl = 0; sl < SL; ++sl) acc3[sl] = zero16;
+        const int half_w = d.Wimg >> 1;
+        float* red = reinterpret_cast<float*>(h1);
+        if constexpr (UBW == 2) {
+            gemm3(0);
+            gemm3(1);
+            __syncthreads();                         // every wave has read its h1 operands
+#pragma unroll
+            for (int sl = 0; sl < SL; ++sl) {
+                float* dst = red + ((size_t)w * kTok + sl * 32 + l32) * kFeat + g * 4;
+                *reinterpret_cast<float4*>(dst) = make_float4(acc3[sl][0], acc3[sl][1], acc3[sl][2], acc3[sl][3]);
+                *reinterpret_cast<float4*>(dst + 8) = make_float4(acc3[sl][4], acc3[sl][5], acc3[sl][6], acc3[sl][7]);
+            }
+            __syncthreads();
+            if (tid < kTok * (kFeat / 4)) {          // as in the 128-token items
+                const int tl = tid & (kTok - 1), c = tid / kTok;
+                float4 sum = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+                for (int ww = 0; ww < kWaves; ++ww) {
+                    const float4 v = *reinterpret_cast<const float4*>(red + ((size_t)ww * kTok + tl) * kFeat + c * 4);
+                    sum = make_float4(sum.x + v.x, sum.y + v.y, sum.z + v.z, sum.w + v.w);
+                }
+                const int tok = tb * kTok + tl, hp = tok / half_w, wp = tok - hp * half_w;
+                float* o = d.Ep + (((size_t)ns * d.N + n) * d.P + jm) * d.D +
+                           ((size_t)c * d.Himg + 2 * hp) * d.Wimg + 2 * wp;
+                *reinterpret_cast<float2*>(o) = make_float2(sum.x, sum.y);
+                *reinterpret_cast<float2*>(o + d.Wimg) = make_float2(sum.z, sum.w);
+            }
+            __syncthreads();                         // red is read before the next item's h1
+        } else {
+            // The wave of the chain's first unit block hands its sums to the wave of the second
+            // (rows 0..15 of the tile: accumulator registers 0..7).
+            const bool first = (ub0 & 1) == 0;
+            float* pass = red + ((size_t)(w & ~1) * SL * 64 + lane) * 8;
+            if (active && first) gemm3(0);
+            __syncthreads();                         // every wave has read its h1 operands
+            if (active && first) {
+#pragma unroll
+                for (int sl = 0; sl < SL; ++sl) {
+                    float4* p = reinterpret_cast<float4*>(pass + (size_t)sl * 64 * 8);
+                    p[0] = make_float4(acc3[sl][0], acc3[sl][1], acc3[sl][2], acc3[sl][3]);
+                    p[1] = make_float4(acc3[sl][4], acc3[sl][5], acc3[sl][6], acc3[sl][7]);
+                }
+            }
+            __syncthreads();
+            if (active && !first) {
+#pragma unroll
+                for (int sl = 0; sl < SL; ++sl) {
+                    const float4* p = reinterpret_cast<const float4*>(pass + (size_t)sl * 64 * 8);
+                    const float4 a = p[0], b = p[1];
+                    acc3[sl][0] = a.x;
+                    acc3[sl][1] = a.y;
+                    acc3[sl][2] = a.z;
+                    acc3[sl][3] = a.w;
+                    acc3[sl][4] = b.x;
+                    acc3[sl][5] = b.y;
+                    acc3[sl][6] = b.z;
+                    acc3[sl][7] = b.w;
+                }
+                gemm3(0);
+                // Lane (g, token): features 4g..4g+3 (channel g) and 8+4g.. (channel 2+g).
+                float* ep = d.Ep + ((size_t)(ub0 >> 1) * d.fine_rows + gm) * d.D;
+#pragma unroll
+                for (int sl = 0; sl < SL; ++sl) {
+                    const int tok = tb * kTok + (sl0 + sl) * 32 + l32, hp = tok / half_w, wp = tok - hp * half_w;
+#pragma unroll
+                    for (int q = 0; q < 2; ++q) {
+                        float* o = ep + ((size_t)(2 * q + g) * d.Himg + 2 * hp) * d.Wimg + 2 * wp;
+                        *reinterpret_cast<float2*>(o) = make_float2(acc3[sl][4 * q], acc3[sl][4 * q + 1]);
+                        *reinterpret_cast<float2*>(o + d.Wimg) = make_float2(acc3[sl][4 * q + 2], acc3[sl][4 * q + 3]);
+                    }
+                }
+            }
+            // The next item's gather touches xs and es only, and its barrier comes before its h1.
+        }
+    }
+}
+
+// Which fine items a launch of M list entries takes, if any: the finest that still fit the blocks
+// in one round. A second round of a finer size costs more than one round of the next (1024
+// tokens, H = 1024: 4 misses in 2 rounds of 32 x 256 26 us, in one of 32 x 512 20 us; 2 misses in
+// 2 rounds of 32 x 128 21 us, in one of 32 x 256 15 us), and two rounds of 64 x 512 more than one
+// of 128-token halves (12 misses: 50 against 41 us).
+enum FineChoice { FINE_NONE, FINE_32x128, FINE_32x256, FINE_32x512, FINE_64x512 };
+template <int H>
+__device__ __forceinline__ int fine_choice(int M, int ntok, int fine_rows, int G) {
+    const int sl = M * (ntok / 32);                  // 32-token slices
+    if (sl / 2 * (H / 512) > G) return FINE_NONE;
+    if (sl * (H / 512) > G) return FINE_64x512;
+    if (sl * (H / 256) > G || M > fine_rows) return FINE_32x512;
+    return sl * (H / 128) > G ? FINE_32x256 : FINE_32x128;
+}
+
+// TOK: tokens per work item, 128; or 64 for launches of a single latent of a wide network (H = 2048)
+// whose items of 32 tokens x 512 units do not fit the blocks in one round: its h1 GELUs meet the W2
+// stream, where a fine item of 64 tokens takes them in turn (2304 tokens: 39 against 43 us).
 template <int H, int TOK>
 __global__ __launch_bounds__(kWaves * 64) void k_eps_mlp(Dev d) {
     constexpr int NT = kWaves * 64;
@@ -137,6 +407,9 @@ __global__ __launch_bounds__(kWaves * 64) void k_eps_mlp(Dev d) {
     float* red = reinterpret_cast<float*>(&h1s[1][0]);
     static_assert(kWaves * kTok * kFeat * 4 <= kTok * HRow * 2, "reduction buffer must fit");
     static_assert(KCH % 2 == 0, "the last chunk of either order is consumed from buffer 1");
+    static_assert(TOK < kTokMax || (32 * (H + 8) <= 2 * kTok * HRow &&
+                                    64 * ((H < 1024 ? H : 1024) + 8) <= 2 * kTok * HRow),
+                  "h1 of a fine item must fit");
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave index, in a scalar register
@@ -199,20 +472,31 @@ __global__ __launch_bounds__(kWaves * 64) void k_eps_mlp(Dev d) {
     // 15/16 x NS x the rounds of whole items do not exceed the rounds of half items spread
     // over all blocks: with one item per block when more than half of the blocks get one,
     // and always from about 7 rounds on.
-    const bool whole = d.eps_whole != nullptr && NS <= 2 &&
+    const bool whole = d.whole_ok && NS <= 2 &&
                        15 * NS * ((tblocks + G - 1) / G) <= 16 * ((tblocks * NS + G - 1) / G);
-    if (d.eps_whole != nullptr && blockIdx.x == 0 && tid == 0) *d.eps_whole = whole ? 1 : 0;
+    const int fine = TOK == kTokMax && d.eps_mode != nullptr ? fine_choice<H>(mpre[d.N], d.ntok, d.fine_rows, G)
+                                                             : FINE_NONE;
+    if (d.eps_mode != nullptr && blockIdx.x == 0 && tid <= d.N)
+        d.eps_mode[tid] = tid > 0 ? mpre[tid - 1]
+                                  : (fine == FINE_32x128 || fine == FINE_32x256
+                                         ? EPS_FINE
+                                         : (fine == FINE_NONE && whole ? EPS_WHOLE : EPS_SPLIT));
+    if constexpr (TOK == kTokMax) if (fine != FINE_NONE) {
+        __bf16* hf = &h1s[0][0];
+        switch (fine) {
+            case FINE_32x128: fine_items<H, 1, 128>(d, hf, xs, es, mpre, fmiss, fnewest); break;
+            case FINE_32x256: fine_items<H, 1, 256>(d, hf, xs, es, mpre, fmiss, fnewest); break;
+            case FINE_32x512: fine_items<H, 1, 512>(d, hf, xs, es, mpre, fmiss, fnewest); break;
+            default: fine_items<H, 2, 512, (H > 1024 ? 2 : 1)>(d, hf, xs, es, mpre, fmiss, fnewest); break;
+        }
+        return;
+    }
     const int g = lane >> 5, l32 = lane & 31;
     // W2^T as a buffer resource (out-of-range loads would return zero)
     const __amdgpu_buffer_rsrc_t w2r = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<__bf16*>(d.w2f), (short)0, H * H * 2, 0x00020000);
     const f32x16 zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f,
                            0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    // K-chunk taken at position i: natural order for even halves; odd halves start with the
-    // chunk a whole-output block still holds in buffer 0 (KCH - 2), then KCH - 1, KCH - 3, ..., 0.
-    auto korder = [&](int odd, int i) {
-        return !odd ? i : (i == 0 ? KCH - 2 : (i == 1 ? KCH - 1 : KCH - 1 - i));
-    };
     float4 run = make_float4(0.f, 0.f, 0.f, 0.f);   // whole outputs: sum of the halves so far
     // One half (output units [512 ns, 512 ns + 512)) of the item (list entry gm, token block tb).
     // WHOLE: part of a whole-output block's item (ns > 0: the gather and the first h1 chunk of
@@ -298,7 +582,7 @@ __global__ __launch_bounds__(kWaves * 64) void k_eps_mlp(Dev d) {
             h1_gelu(buf, kc, tb4, 2);
         };
         if (!reuse) {
-            const int k0 = korder(odd, 0);
+            const int k0 = korder<KCH>(odd, 0);
             h1_setup(k0);
 #pragma unroll
             for (int tb4 = 0; tb4 < TB4; ++tb4) h1_slice(h1s[0], k0, tb4);
@@ -354,8 +638,8 @@ __global__ __launch_bounds__(kWaves * 64) void k_eps_mlp(Dev d) {
         // GELU slice).
         auto chunk = [&](int i, auto more_c) {
             constexpr bool more = decltype(more_c)::value;
-            const int kc = korder(odd, i);
-            const int kn = more ? korder(odd, i + 1) : 0;
+            const int kc = korder<KCH>(odd, i);
+            const int kn = more ? korder<KCH>(odd, i + 1) : 0;
             if constexpr (more) h1_setup(kn);
             __bf16* nbuf = h1s[(i + 1) & 1];
             const __bf16* h1b = h1s[i & 1] + l32 * HRow + g * 8;
@@ -384,7 +668,7 @@ __global__ __launch_bounds__(kWaves * 64) void k_eps_mlp(Dev d) {
             }
             __syncthreads();                 // chunk kc + 1 complete; chunk kc's buffer free
         };
-        load_a(A0, korder(odd, 0), 0);
+        load_a(A0, korder<KCH>(odd, 0), 0);
         for (int i = 0; i + 1 < KCH; ++i) chunk(i, std::true_type{});
         chunk(KCH - 1, std::false_type{});
 
@@ -534,15 +818,19 @@ int mlp_splits(int hidden) { return hidden / kNH; }
 
 int mlp_grid_size(int device_cus) { return device_cus > 0 ? device_cus : 256; }
 
+int mlp_fine_rows(int hidden, int ntok, int grid) {
+    const long long rows = 2ll * grid * 64 * 256 / ((long long)ntok * hidden);
+    return rows < 1 ? 1 : (int)rows;
+}
+
 hipError_t launch_eps_mlp(const Dev& d, hipStream_t st, hipEvent_t start, hipEvent_t stop, int single) {
     const dim3 grid(d.mlp_grid), block(kWaves * 64);
-    switch (d.hidden * 2 + (single ? 1 : 0)) {
-        case 512 * 2: hipExtLaunchKernelGGL((k_eps_mlp<512, 128>), grid, block, 0, st, start, stop, 0, d); break;
-        case 512 * 2 + 1: hipExtLaunchKernelGGL((k_eps_mlp<512, 64>), grid, block, 0, st, start, stop, 0, d); break;
-        case 1024 * 2: hipExtLaunchKernelGGL((k_eps_mlp<1024, 128>), grid, block, 0, st, start, stop, 0, d); break;
-        case 1024 * 2 + 1: hipExtLaunchKernelGGL((k_eps_mlp<1024, 64>), grid, block, 0, st, start, stop, 0, d); break;
-        case 2048 * 2: hipExtLaunchKernelGGL((k_eps_mlp<2048, 128>), grid, block, 0, st, start, stop, 0, d); break;
-        case 2048 * 2 + 1: hipExtLaunchKernelGGL((k_eps_mlp<2048, 64>), grid, block, 0, st, start, stop, 0, d); break;
+    const bool tok64 = single && d.hidden == 2048 && d.ntok / 32 * (d.hidden / 512) > d.mlp_grid;
+    switch (d.hidden + (tok64 ? 1 : 0)) {
+        case 512: hipExtLaunchKernelGGL((k_eps_mlp<512, 128>), grid, block, 0, st, start, stop, 0, d); break;
+        case 1024: hipExtLaunchKernelGGL((k_eps_mlp<1024, 128>), grid, block, 0, st, start, stop, 0, d); break;
+        case 2048: hipExtLaunchKernelGGL((k_eps_mlp<2048, 128>), grid, block, 0, st, start, stop, 0, d); break;
+        case 2048 + 1: hipExtLaunchKernelGGL((k_eps_mlp<2048, 64>), grid, block, 0, st, start, stop, 0, d); break;
         default:
             return hipErrorInvalidValue;
     }

@@ -48,6 +48,22 @@ __device__ __forceinline__ float4 f4_fresh(const Dev& d, int n, int c4, int t, f
         return make_float4(c * x.x, c * x.y, c * x.z, c * x.w);
     }
     const size_t D = (size_t)d.D;
+    if (*d.eps_mode == EPS_FINE) {
+        // 64-unit partials: the sum of each half's in order, then the halves' in order.
+        const float* ep = d.Ep + (size_t)d.eps_mode[1 + n] * D;
+        float4 e = make_float4(0.f, 0.f, 0.f, 0.f);
+        for (int h = 0; h < d.nsplit; ++h) {
+            float4 v[kFineGroups], s = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+            for (int w = 0; w < kFineGroups; ++w)
+                v[w] = reinterpret_cast<const float4*>(ep + (size_t)(h * kFineGroups + w) * d.fine_rows * D)[c4];
+#pragma unroll
+            for (int w = 0; w < kFineGroups; ++w)
+                s = make_float4(s.x + v[w].x, s.y + v[w].y, s.z + v[w].z, s.w + v[w].w);
+            e = h == 0 ? s : make_float4(e.x + s.x, e.y + s.y, e.z + s.z, e.w + s.w);
+        }
+        return e;
+    }
     const float* ep = d.Ep + (size_t)n * d.P * D;
     float4 e = reinterpret_cast<const float4*>(ep)[c4];
     for (int h = 1; h < d.nsplit; ++h) {

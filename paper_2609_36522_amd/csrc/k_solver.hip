@@ -172,7 +172,8 @@ __global__ __launch_bounds__(COLS * ROWS, MINB) void k_picard(Dev d) {
     const Ctrl* ctrl = d.ctrl + n;
     // The network launch wrote the fresh outputs of the misses into Eh (whole outputs) rather
     // than split partials into Ep.
-    const bool whole = !LINEAR && d.eps_whole != nullptr && *d.eps_whole != 0;
+    const int mode = !LINEAR && d.eps_mode != nullptr ? *d.eps_mode : EPS_SPLIT;
+    const bool whole = mode == EPS_WHOLE;
     if (ctrl->done) return;
     const int s = ctrl->s, e = ctrl->e, W = e - s, newest = ctrl->newest;
     const int tid = threadIdx.x;
@@ -187,12 +188,37 @@ __global__ __launch_bounds__(COLS * ROWS, MINB) void k_picard(Dev d) {
     float* Eh = d.Eh + (size_t)n * d.T * D;
     const float* noise = NOISE ? d.noise + (size_t)n * d.T * D : nullptr;
 
+    // ---- 64-unit partial outputs of the misses (a launch of few misses): the sum of each half's in
+    // order, then the halves'. Before any other load, so that no register is held beside theirs.
+    float4 e0[TPT];
+#pragma unroll
+    for (int k = 0; k < TPT; ++k) e0[k] = f4_zero();
+    if (!LINEAR && mode == EPS_FINE) {
+#pragma unroll
+        for (int k = 0; k < TPT; ++k) {
+            const int j = j0 + k;
+            if (!(j < W && colok && ctrl->slot_miss[j])) continue;
+            const float* fp = d.Ep + (size_t)(d.eps_mode[1 + n] + ctrl->slot_rank[j]) * D;
+#pragma unroll 1
+            for (int h = 0; h < NS; ++h) {
+                float4 p[kFineGroups], a = f4_zero();
+#pragma unroll
+                for (int w = 0; w < kFineGroups; ++w)
+                    p[w] = reinterpret_cast<const float4*>(fp + (size_t)(h * kFineGroups + w) * d.fine_rows * D)[c4];
+#pragma unroll
+                for (int w = 0; w < kFineGroups; ++w)
+                    a = make_float4(a.x + p[w].x, a.y + p[w].y, a.z + p[w].z, a.w + p[w].w);
+                e0[k] = h == 0 ? a : make_float4(e0[k].x + a.x, e0[k].y + a.y, e0[k].z + a.z, e0[k].w + a.w);
+            }
+        }
+    }
+
     // ---- the states (independent of the miss list) first; meanwhile the block stages the
     // per-slot miss flags and ranks in LDS, so that the address of every other load is known
     // after one barrier instead of a chain of dependent global byte loads.
     // xs[k] = current estimate of state s + j0 + k (k <= TPT, j0 + k <= W): the drift input of
     // slot j0 + k and the previous iterate of the state slot j0 + k - 1 updates.
-    float4 xs[TPT + 1], e0[TPT], ex[TPT][NS > 1 ? NS - 1 : 1], zt[TPT], xhn[TPT];
+    float4 xs[TPT + 1], ex[TPT][NS > 1 ? NS - 1 : 1], zt[TPT], xhn[TPT];
     double cf[TPT][3];
     float4 anchor = f4_zero();
     if (colok) anchor = reinterpret_cast<const float4*>(X + min(s, newest) * D)[c4];
@@ -208,7 +234,6 @@ __global__ __launch_bounds__(COLS * ROWS, MINB) void k_picard(Dev d) {
     for (int k = 0; k < TPT; ++k) {
         const int j = j0 + k, t = s + j;
         const bool act = j < W && colok;
-        e0[k] = f4_zero();
         zt[k] = f4_zero();
         xhn[k] = f4_zero();
 #pragma unroll
@@ -252,8 +277,9 @@ __global__ __launch_bounds__(COLS * ROWS, MINB) void k_picard(Dev d) {
             // Eq. (6): the cached output of a hit, or the network kernel's split partial
             // outputs of a miss (LINEAR: computed below from the state).
             const float* ep = d.Ep + ((size_t)n * d.P + rk[k]) * D;
-            if (!(LINEAR && miss)) e0[k] = reinterpret_cast<const float4*>(miss ? ep : Eh + t * D)[c4];
-            if (!LINEAR && miss) {
+            const bool fine = !LINEAR && miss && mode == EPS_FINE;
+            if (!(LINEAR && miss) && !fine) e0[k] = reinterpret_cast<const float4*>(miss ? ep : Eh + t * D)[c4];
+            if (!LINEAR && miss && !fine) {
 #pragma unroll
                 for (int h = 1; h < NS; ++h)
                     ex[k][h - 1] = reinterpret_cast<const float4*>(ep + (size_t)h * d.N * d.P * D)[c4];
@@ -278,7 +304,7 @@ __global__ __launch_bounds__(COLS * ROWS, MINB) void k_picard(Dev d) {
                 if (LINEAR) {
                     const float ct = d.lin_c[t];
                     eps = make_float4(ct * x.x, ct * x.y, ct * x.z, ct * x.w);
-                } else if (!whole) {
+                } else if (mode == EPS_SPLIT) {
                     // Fresh output = fixed-order sum of the network kernel's partials.
 #pragma unroll
                     for (int h = 1; h < NS; ++h) {

@@ -36,6 +36,14 @@ struct SlidePre {
     int64_t nfe, hits, revisits, revisits_below;
 };
 
+// Where a network launch left the fresh outputs of the misses.
+enum EpsMode : int32_t {
+    EPS_SPLIT = 0,      // one partial output per half of 512 units, in Ep
+    EPS_WHOLE = 1,      // whole outputs, in Eh
+    EPS_FINE = 2        // one partial output per 64 units, in Ep by list entry
+};
+constexpr int kFineGroups = 8;  // 64-unit partial outputs per half
+
 // Geometry and device buffers handed to every kernel launcher. Per-sample buffers are
 // stacked along a leading sample index n < N.
 struct Dev {
@@ -66,10 +74,14 @@ struct Dev {
     const __bf16* w2f;         // W2^T fragment-major: [hidden/32][hidden/16][64 lanes][8]
     const __bf16* w3p;         // [hidden/32][2][64][8] lane-permuted W3 fragments
     float* temb;               // [T][hidden]      e_j = temb(t_j) Wt
-    float* Ep;                 // [nsplit][N][P][D] per-half network outputs of the misses
+    float* Ep;                 // partial outputs of the misses: [nsplit][N][P][D] per half, or
+                               // [hidden / 64][fine_rows][D] per 64 units of a list entry
     int32_t nsplit;            // halves of the output units (partials summed by k_picard)
-    int32_t* eps_whole;        // [1] set by each network launch: 1 = it wrote whole outputs
-                               // into Eh, 0 = split partials into Ep; null = always split
+    int32_t* eps_mode;         // [1 + N] set by each network launch: where the fresh outputs are
+                               // (EpsMode), then each sample's first entry in the list of
+                               // misses; null = always EPS_SPLIT
+    int32_t whole_ok;          // whole outputs may be written into Eh
+    int32_t fine_rows;         // list entries whose partial outputs per 64 units fit Ep (EPS_FINE)
     int32_t picard_blocks;
     int32_t mlp_grid;
     // Parareal sampler only (k_parareal.hip)
@@ -89,8 +101,10 @@ hipError_t launch_slide_pending(const Dev& d, hipStream_t st);
 // Largest fp64 partial-sum volume per sample the network kernel reduces redundantly per block.
 constexpr size_t kFusedSlideMaxBytes = 256 * 1024;
 hipError_t launch_picard(const Dev& d, hipStream_t st, int linear, hipEvent_t start, hipEvent_t stop);
-// single: the launch evaluates at most one latent (64-token work items).
+// single: the launch evaluates at most one latent.
 hipError_t launch_eps_mlp(const Dev& d, hipStream_t st, hipEvent_t start, hipEvent_t stop, int single = 0);
+// List entries up to which a launch may take items that leave partial outputs per 64 units.
+int mlp_fine_rows(int hidden, int ntok, int grid);
 // Rearranges the patch-MLP weights ([in][out] bf16 bit patterns, device) into the network
 // kernel's layouts: w1t [H][16], w2f (W2^T fragments, halved), w3p (lane-permuted W3
 // fragments, halved).

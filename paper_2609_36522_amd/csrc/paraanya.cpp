@@ -232,8 +232,10 @@ int setup_handle(paraanya* h, const Request& q, const double* coef, const double
         d.noise = h->noise_buf;
     }
     // Whole network outputs written straight into the cache (unless split ones are forced).
-    if (q.em->kind == PA_EPS_PATCH_MLP && !(h->flags & PA_FLAG_SPLIT_OUTPUTS))
-        if ((rc = h->alloc(&d.eps_whole, 1, "eps_whole"))) return rc;
+    if (q.em->kind == PA_EPS_PATCH_MLP && !(h->flags & PA_FLAG_SPLIT_OUTPUTS)) {
+        if ((rc = h->alloc(&d.eps_mode, 1 + Nz, "eps_mode"))) return rc;
+        d.whole_ok = 1;
+    }
     // setup_network takes all its buffers before it enqueues anything, so a request that does
     // not fit fails before the first upload.
     if ((rc = pa::setup_network(d, h->mem, q.em, tv, cus, Nz * P, h->stream))) return rc;

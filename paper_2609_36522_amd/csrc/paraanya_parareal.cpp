@@ -64,8 +64,6 @@ struct paraanya_parareal {
                 const int rc = timer.pair(0, &e0, &e1);
                 if (rc) return rc;
             }
-            // A coarse request evaluates one latent: 64-token work items spread it over twice
-            // as many CUs.
             PA_HIP(pa::launch_eps_mlp(d, stream, e0, e1, step_kernel == pa::PRK_COARSE ? 1 : 0));
         }
         PA_HIP(pa::launch_pr(d, a, step_kernel, stream));
@@ -180,6 +178,8 @@ int paraanya_parareal_create(const int32_t latent_shape[4], int32_t T, const pa_
     if (he != hipSuccess) return bail(hip_fail(he, "hipMemcpyAsync(pr_coef)"));
     he = hipMemsetAsync(d.ctrl, 0, Bz * sizeof(Ctrl), h->stream);
     if (he != hipSuccess) return bail(hip_fail(he, "hipMemsetAsync(ctrl)"));
+    if (h->model == PA_EPS_PATCH_MLP)
+        if ((rc = m.alloc(&d.eps_mode, 1 + Bz, "eps_mode"))) return bail(rc);
     if ((rc = pa::setup_network(d, m, eps_model, tv.data(), cus, Bz, h->stream))) return bail(rc);
     // The host vectors above die at return: wait for the copies that read them.
     he = hipStreamSynchronize(h->stream);

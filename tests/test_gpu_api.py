@@ -306,6 +306,31 @@ def test_whole_outputs_equal_split_outputs(wl, batch, gpu_lib):
             assert np.array_equal(A, Bv), n
 
 
+# (latent, H, window, samples): on 256 CUs the misses of one window in items of 32 tokens x 128,
+# 256 and 512 units and 64 tokens x 512 units (whole K, half of K at H = 2048), at the most misses
+# each takes and the fewest of the next, up to the first launch of 128-token items.
+FINE_SHAPES = [((4, 64, 64), 1024, P, 1) for P in (1, 2, 3, 4, 5, 8, 9)] + \
+              [((4, 32, 32), 512, P, 1) for P in (1, 8, 9, 16, 17, 32, 33, 64, 65)] + \
+              [((4, 16, 32), 2048, P, 1) for P in (1, 4, 5, 8, 9, 16, 17, 32, 33)] + \
+              [((4, 32, 96), 1024, 1, 3), ((4, 48, 64), 2048, 1, 2), ((4, 32, 32), 512, 2, 9)]
+
+
+@pytest.mark.parametrize("latent,hidden,P,batch", FINE_SHAPES)
+def test_few_misses_equal_split_outputs(latent, hidden, P, batch, gpu_lib):
+    """Launches of few misses take smaller work items; the cache and the states are bit for bit
+    those of a handle held to 128-token items with split outputs. One window, one sweep."""
+    xb = torch.from_numpy(inputs.x_init_batch(latent, batch).reshape(-1)).cuda()
+    res = []
+    for split in (False, True):
+        with B.Sampler(latent, P, P, 0.0, math.inf, "patch_mlp", weights=inputs.mlp_weights(hidden),
+                       hidden=hidden, batch=batch, split_outputs=split) as s:
+            out = s.sample(xb).cpu().numpy()
+            assert s.stats()["nfe"] == batch * P
+            res.append([out] + [a for n in range(batch) for a in s.read_state(0, None, n)])
+    for a, b in zip(*res):
+        assert np.array_equal(a, b)
+
+
 @pytest.mark.parametrize("wl,batch", [(W.TINY_LINEAR, 3), (W.SMALL_MLP, 1)], ids=["linear_batch3", "mlp"])
 def test_sample_output_alignment(wl, batch, gpu_lib):
     """Buffers at any 4-byte offset and an aliased x_init == x_out give the same final
