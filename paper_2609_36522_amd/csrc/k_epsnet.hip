@@ -131,10 +131,18 @@ __device__ __forceinline__ int korder(int odd, int i) {
 // per item while CUs are free. Launch time with 128-token items -> with these (1024 tokens,
 // H = 1024): 1 miss 34 -> 12 us, 2 misses 35 -> 15, 4 36 -> 20, 8 38 -> 28; 256 tokens, H = 512:
 // 16 misses 26 -> 11 us; 768 tokens, H = 2048: 1 miss 59 -> 27 us, 5 misses 67 -> 52.
-template <int H, int TS, int UF, int KP = 1>
+// WHOLE: the item is all units of its tokens, half after half from one h1, and its output goes
+// straight into the cache like that of a whole 128-token item.
+// map(item): list entry, token block of 32 TS tokens and unit group of an item.
+struct FineItem {
+    int gm, tb, ug;
+};
+template <int H, int TS, int UF, int KP, bool WHOLE, class Map>
 __device__ __forceinline__ void fine_items(const Dev& d, __bf16* h1, __bf16* xs, float* es, const int* mpre,
-                                           const int* fmiss, int fnewest) {
-    constexpr int NT = kWaves * 64, kTok = 32 * TS, HP = H / KP, HR = HP + 8, KS = H / 16, KCH = H / kKC, NUG = H / UF;
+                                           const int* fmiss, int fnewest, int items, Map map) {
+    constexpr int NT = kWaves * 64, kTok = 32 * TS, HP = H / KP, HR = HP + 8, KS = H / 16, KCH = H / kKC;
+    constexpr int NH = WHOLE ? H / kNH : 1;          // halves the item takes in turn
+    static_assert(!WHOLE || (UF == kNH && KP == 1), "h1 of all units serves every half");
     constexpr int UBW = UF == 512 ? 2 : 1;           // 32-unit blocks per wave
     constexpr int UB = UF / 32;                      // 32-unit blocks per item
     constexpr bool kSplitTok = UB == 4 && TS > 1;    // two wave groups, each half of the token slices
@@ -150,31 +158,32 @@ __device__ __forceinline__ void fine_items(const Dev& d, __bf16* h1, __bf16* xs,
         const_cast<__bf16*>(d.w2f), (short)0, H * H * 2, 0x00020000);
     const f32x16 zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f,
                            0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    const int nb = d.ntok / kTok, items = mpre[d.N] * nb * NUG;
     const bool active = UB >= 8 || kSplitTok || w < UB;
     const int sl0 = kSplitTok ? (w >> 2) * SL : 0;   // this wave's first token slice
     for (int item = blockIdx.x; item < items; item += gridDim.x) {
-        // Unit groups fastest: with the blocks dealt to the XCDs in turn, an XCD's L2 fills with
-        // the W2 columns of few groups.
-        const int ug = item % NUG, tb = (item / NUG) % nb, gm = item / NUG / nb;
+        const FineItem it = map(item);
+        const int gm = it.gm, tb = it.tb;
         int n = 0;
         while (mpre[n + 1] <= gm) ++n;               // sample of list entry gm (uniform)
         const int jm = gm - mpre[n];
         const Ctrl* ctrl = d.ctrl + n;
         const int t = d.fused_slide ? fmiss[jm] : ctrl->miss_idx[jm];
         const int newest = d.fused_slide ? fnewest : ctrl->newest;
-        const int ns = ug * UF / kNH, odd = ns & 1;
-        const int ub0 = ug * UB + (UB == 4 ? (w & 3) : w * UBW);   // this wave's first unit block
+        const int ns0 = WHOLE ? 0 : it.ug * UF / kNH;
+        const int ub00 = it.ug * UB + (UB == 4 ? (w & 3) : w * UBW);   // this wave's first unit block
 
         // ---- W2^T fragments of the first k-steps, then the gather: one round trip to memory
         bf16x8 A[DEPTH][UBW];
-        auto load_a = [&](int i, int j) {            // k-step i of the half's order, into stage j
-            const int ks = korder<KCH>(odd, i / 16) * 16 + i % 16;
+        auto load_a = [&](int hf, int i, int j) {    // k-step i of the half's order, into stage j
+            const int ks = korder<KCH>((ns0 + hf) & 1, i / 16) * 16 + i % 16;
+            const int ub0 = ub00 + hf * (kNH / 32);
 #pragma unroll
             for (int u = 0; u < UBW; ++u)
                 A[j][u] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(
                     w2r, lane * 16, ((ub0 + u) * KS + ks) * 64 * 16, 0));
         };
+        // K-chunk in place q of pass ps of h1 (KP = 1: in natural order, for either order of a half)
+        auto h1_chunk = [&](int ps, int q) { return KP == 1 ? q : korder<KCH>(ns0 & 1, ps * KCP + q); };
         const float* xt = d.X + ((size_t)n * (d.T + 1) + min(t, newest)) * d.D;
         const float* et = d.temb + (size_t)t * H;
         constexpr int kPer = kTok * kFeat / NT, kEs = (H / 4 + NT - 1) / NT;
@@ -185,7 +194,7 @@ __device__ __forceinline__ void fine_items(const Dev& d, __bf16* h1, __bf16* xs,
 #pragma unroll
             for (int q = 0; q < KCP; ++q)
                 w1a[q] = *reinterpret_cast<const bf16x8*>(
-                    d.w1t + (size_t)(korder<KCH>(odd, ps * KCP + q) * kKC + w * 32 + l32) * kFeat + g * 8);
+                    d.w1t + (size_t)(h1_chunk(ps, q) * kKC + w * 32 + l32) * kFeat + g * 8);
         };
 #pragma unroll
         for (int k = 0; k < kPer; ++k) xv[k] = xt[tok_pos<kTok>(tid + k * NT, tb, d.Himg, d.Wimg).idx];
@@ -195,7 +204,7 @@ __device__ __forceinline__ void fine_items(const Dev& d, __bf16* h1, __bf16* xs,
         load_w1(0);
         if (active) {
 #pragma unroll
-            for (int j = 0; j < DEPTH; ++j) load_a(j, j);
+            for (int j = 0; j < DEPTH; ++j) load_a(0, j, j);
         }
 #pragma unroll
         for (int k = 0; k < kPer; ++k) {
@@ -208,34 +217,37 @@ __device__ __forceinline__ void fine_items(const Dev& d, __bf16* h1, __bf16* xs,
         __syncthreads();
 
         f32x16 acc[UBW][SL];
-#pragma unroll
-        for (int u = 0; u < UBW; ++u)
-#pragma unroll
-            for (int sl = 0; sl < SL; ++sl) acc[u][sl] = zero16;
         const __bf16* hb = h1 + (sl0 * 32 + l32) * HR + g * 8;
-        // DEPTH k-steps from the pass's k-step p0 (i0 of the half's order); reloads the stages
-        // if more follow.
-        auto steps = [&](int i0, int p0, auto more_c) {
+        // DEPTH k-steps from k-step i0 of the half's order; reloads the stages if more follow.
+        constexpr int KSP = KS / KP;                 // k-steps per pass
+        auto steps = [&](int hf, int i0, auto more_c) {
+            const int p0 = KP == 1 ? korder<KCH>((ns0 + hf) & 1, i0 / 16) * kKC + (i0 % 16) * 16 : i0 % KSP * 16;
 #pragma unroll
             for (int j = 0; j < DEPTH; ++j) {
                 bf16x8 B[SL];
 #pragma unroll
                 for (int sl = 0; sl < SL; ++sl)
-                    B[sl] = *reinterpret_cast<const bf16x8*>(hb + sl * 32 * HR + (p0 + j) * 16);
+                    B[sl] = *reinterpret_cast<const bf16x8*>(hb + sl * 32 * HR + p0 + j * 16);
 #pragma unroll
                 for (int sl = 0; sl < SL; ++sl)
 #pragma unroll
                     for (int u = 0; u < UBW; ++u) acc[u][sl] = mfma32(A[j][u], B[sl], acc[u][sl]);
-                if constexpr (decltype(more_c)::value) load_a(i0 + DEPTH + j, j);
+                if constexpr (decltype(more_c)::value) load_a(hf, i0 + DEPTH + j, j);
             }
         };
-        constexpr int KSP = KS / KP;                 // k-steps per pass
+        auto zero_acc = [&] {
+#pragma unroll
+            for (int u = 0; u < UBW; ++u)
+#pragma unroll
+                for (int sl = 0; sl < SL; ++sl) acc[u][sl] = zero16;
+        };
+        zero_acc();
 #pragma unroll
         for (int ps = 0; ps < KP; ++ps) {
-            // ---- h1 of the pass's units: rows [token][units in the half's K order]
+            // ---- h1 of the pass's units: rows [token][units, chunk by chunk]
 #pragma unroll
             for (int q = 0; q < KCP; ++q) {
-                const int u0 = korder<KCH>(odd, ps * KCP + q) * kKC + w * 32, p0 = q * kKC + w * 32;
+                const int u0 = h1_chunk(ps, q) * kKC + w * 32, p0 = q * kKC + w * 32;
 #pragma unroll
                 for (int sl = 0; sl < TS; ++sl) {
                     const bf16x8 b = *reinterpret_cast<const bf16x8*>(xs + (sl * 32 + l32) * kXRow + g * 8);
@@ -262,16 +274,17 @@ __device__ __forceinline__ void fine_items(const Dev& d, __bf16* h1, __bf16* xs,
             __syncthreads();
             // ---- GEMM2 over them
             if (active) {
-                for (int i = 0; i + DEPTH < KSP; i += DEPTH) steps(ps * KSP + i, i, std::true_type{});
-                if (ps + 1 < KP) steps((ps + 1) * KSP - DEPTH, KSP - DEPTH, std::true_type{});
-                else steps(KS - DEPTH, KSP - DEPTH, std::false_type{});
+                #pragma unroll 1
+                for (int i = 0; i + DEPTH < KSP; i += DEPTH) steps(0, ps * KSP + i, std::true_type{});
+                if (ps + 1 < KP) steps(0, (ps + 1) * KSP - DEPTH, std::true_type{});
+                else steps(0, KS - DEPTH, std::false_type{});
             }
             if (ps + 1 < KP) __syncthreads();        // the pass's h1 is read before the next one's
         }
 
         // ---- GEMM3: chains of 64 units (two unit blocks) per token slice
         f32x16 acc3[SL];
-        auto gemm3 = [&](int u) {
+        auto gemm3 = [&](int ub0, int u) {
 #pragma unroll
             for (int jj = 0; jj < 2; ++jj) {
                 const bf16x8 a3 = *reinterpret_cast<const bf16x8*>(
@@ -290,37 +303,70 @@ __device__ __forceinline__ void fine_items(const Dev& d, __bf16* h1, __bf16* xs,
         const int half_w = d.Wimg >> 1;
         float* red = reinterpret_cast<float*>(h1);
         if constexpr (UBW == 2) {
-            gemm3(0);
-            gemm3(1);
-            __syncthreads();                         // every wave has read its h1 operands
+            // WHOLE: the first half's sums wait in registers (8 per slice) while the second takes
+            // h1, which the reduction overwrites.
+            float keep[SL][8];
+            if constexpr (NH == 2) {
 #pragma unroll
-            for (int sl = 0; sl < SL; ++sl) {
-                float* dst = red + ((size_t)w * kTok + sl * 32 + l32) * kFeat + g * 4;
-                *reinterpret_cast<float4*>(dst) = make_float4(acc3[sl][0], acc3[sl][1], acc3[sl][2], acc3[sl][3]);
-                *reinterpret_cast<float4*>(dst + 8) = make_float4(acc3[sl][4], acc3[sl][5], acc3[sl][6], acc3[sl][7]);
+                for (int j = 0; j < DEPTH; ++j) load_a(1, j, j);
             }
-            __syncthreads();
-            if (tid < kTok * (kFeat / 4)) {          // as in the 128-token items
-                const int tl = tid & (kTok - 1), c = tid / kTok;
-                float4 sum = make_float4(0.f, 0.f, 0.f, 0.f);
+            gemm3(ub00, 0);
+            gemm3(ub00, 1);
+            if constexpr (NH == 2) {
 #pragma unroll
-                for (int ww = 0; ww < kWaves; ++ww) {
-                    const float4 v = *reinterpret_cast<const float4*>(red + ((size_t)ww * kTok + tl) * kFeat + c * 4);
-                    sum = make_float4(sum.x + v.x, sum.y + v.y, sum.z + v.z, sum.w + v.w);
+                for (int sl = 0; sl < SL; ++sl) {
+#pragma unroll
+                    for (int r = 0; r < 8; ++r) keep[sl][r] = acc3[sl][r];
+                    acc3[sl] = zero16;
                 }
-                const int tok = tb * kTok + tl, hp = tok / half_w, wp = tok - hp * half_w;
-                float* o = d.Ep + (((size_t)ns * d.N + n) * d.P + jm) * d.D +
-                           ((size_t)c * d.Himg + 2 * hp) * d.Wimg + 2 * wp;
-                *reinterpret_cast<float2*>(o) = make_float2(sum.x, sum.y);
-                *reinterpret_cast<float2*>(o + d.Wimg) = make_float2(sum.z, sum.w);
+                zero_acc();
+                #pragma unroll 1
+                for (int i = 0; i + DEPTH < KS; i += DEPTH) steps(1, i, std::true_type{});
+                steps(1, KS - DEPTH, std::false_type{});
+                gemm3(ub00 + kNH / 32, 0);
+                gemm3(ub00 + kNH / 32, 1);
+            }
+            float4 run = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+            for (int hf = 0; hf < NH; ++hf) {
+                __syncthreads();                         // h1 operands, or the last half's sums, are read
+#pragma unroll
+                for (int sl = 0; sl < SL; ++sl) {
+                    float* dst = red + ((size_t)w * kTok + sl * 32 + l32) * kFeat + g * 4;
+                    const bool kept = NH == 2 && hf == 0;
+                    float v[8];
+#pragma unroll
+                    for (int r = 0; r < 8; ++r) v[r] = kept ? keep[sl][r] : acc3[sl][r];
+                    *reinterpret_cast<float4*>(dst) = make_float4(v[0], v[1], v[2], v[3]);
+                    *reinterpret_cast<float4*>(dst + 8) = make_float4(v[4], v[5], v[6], v[7]);
+                }
+                __syncthreads();
+                if (tid < kTok * (kFeat / 4)) {          // as in the 128-token items
+                    const int tl = tid & (kTok - 1), c = tid / kTok;
+                    float4 sum = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+                    for (int ww = 0; ww < kWaves; ++ww) {
+                        const float4 v = *reinterpret_cast<const float4*>(red + ((size_t)ww * kTok + tl) * kFeat + c * 4);
+                        sum = make_float4(sum.x + v.x, sum.y + v.y, sum.z + v.z, sum.w + v.w);
+                    }
+                    run = hf == 0 ? sum : make_float4(run.x + sum.x, run.y + sum.y, run.z + sum.z, run.w + sum.w);
+                    if (hf == NH - 1) {
+                        const int tok = tb * kTok + tl, hp = tok / half_w, wp = tok - hp * half_w;
+                        float* out = WHOLE ? d.Eh + ((size_t)n * d.T + t) * d.D
+                                           : d.Ep + (((size_t)ns0 * d.N + n) * d.P + jm) * d.D;
+                        float* o = out + ((size_t)c * d.Himg + 2 * hp) * d.Wimg + 2 * wp;
+                        *reinterpret_cast<float2*>(o) = make_float2(run.x, run.y);
+                        *reinterpret_cast<float2*>(o + d.Wimg) = make_float2(run.z, run.w);
+                    }
+                }
             }
             __syncthreads();                         // red is read before the next item's h1
         } else {
             // The wave of the chain's first unit block hands its sums to the wave of the second
             // (rows 0..15 of the tile: accumulator registers 0..7).
-            const bool first = (ub0 & 1) == 0;
+            const bool first = (ub00 & 1) == 0;
             float* pass = red + ((size_t)(w & ~1) * SL * 64 + lane) * 8;
-            if (active && first) gemm3(0);
+            if (active && first) gemm3(ub00, 0);
             __syncthreads();                         // every wave has read its h1 operands
             if (active && first) {
 #pragma unroll
@@ -345,9 +391,9 @@ __device__ __forceinline__ void fine_items(const Dev& d, __bf16* h1, __bf16* xs,
                     acc3[sl][6] = b.z;
                     acc3[sl][7] = b.w;
                 }
-                gemm3(0);
+                gemm3(ub00, 0);
                 // Lane (g, token): features 4g..4g+3 (channel g) and 8+4g.. (channel 2+g).
-                float* ep = d.Ep + ((size_t)(ub0 >> 1) * d.fine_rows + gm) * d.D;
+                float* ep = d.Ep + ((size_t)(ub00 >> 1) * d.fine_rows + gm) * d.D;
 #pragma unroll
                 for (int sl = 0; sl < SL; ++sl) {
                     const int tok = tb * kTok + (sl0 + sl) * 32 + l32, hp = tok / half_w, wp = tok - hp * half_w;
@@ -483,11 +529,22 @@ __global__ __launch_bounds__(kWaves * 64) void k_eps_mlp(Dev d) {
                                          : (fine == FINE_NONE && whole ? EPS_WHOLE : EPS_SPLIT));
     if constexpr (TOK == kTokMax) if (fine != FINE_NONE) {
         __bf16* hf = &h1s[0][0];
+        // Unit groups fastest: with the blocks dealt to the XCDs in turn, an XCD's L2 fills with
+        // the W2 columns of few groups.
+        auto take = [&](auto ts_c, auto uf_c, auto kp_c) {
+            constexpr int TS = decltype(ts_c)::value, NUG = H / decltype(uf_c)::value;
+            const int nb = d.ntok / (32 * TS);
+            fine_items<H, TS, decltype(uf_c)::value, decltype(kp_c)::value, false>(
+                d, hf, xs, es, mpre, fmiss, fnewest, mpre[d.N] * nb * NUG,
+                [=](int i) { return FineItem{i / NUG / nb, i / NUG % nb, i % NUG}; });
+        };
+        typedef std::integral_constant<int, 1> c1;
+        typedef std::integral_constant<int, 2> c2;
         switch (fine) {
-            case FINE_32x128: fine_items<H, 1, 128>(d, hf, xs, es, mpre, fmiss, fnewest); break;
-            case FINE_32x256: fine_items<H, 1, 256>(d, hf, xs, es, mpre, fmiss, fnewest); break;
-            case FINE_32x512: fine_items<H, 1, 512>(d, hf, xs, es, mpre, fmiss, fnewest); break;
-            default: fine_items<H, 2, 512, (H > 1024 ? 2 : 1)>(d, hf, xs, es, mpre, fmiss, fnewest); break;
+            case FINE_32x128: take(c1{}, std::integral_constant<int, 128>{}, c1{}); break;
+            case FINE_32x256: take(c1{}, std::integral_constant<int, 256>{}, c1{}); break;
+            case FINE_32x512: take(c1{}, std::integral_constant<int, 512>{}, c1{}); break;
+            default: take(c2{}, std::integral_constant<int, 512>{}, std::integral_constant<int, (H > 1024 ? 2 : 1)>{}); break;
         }
         return;
     }
@@ -743,9 +800,47 @@ __global__ __launch_bounds__(kWaves * 64) void k_eps_mlp(Dev d) {
 
     // One block item: both halves of a token block (whole) or one half (split).
     const int per = whole ? NS : 1;
-    for (int item = blockIdx.x; item < tblocks * (NS / per); item += G) {
+    const int units = tblocks * (NS / per);
+    // The items beyond the last full round, if they are few, are cut into items of 32 or 64 tokens
+    // (fine_items), so that the launch ends with one short item per block instead of a long one
+    // on few. Up to a quarter of the blocks' number: 32 tokens (3/16 for whole outputs of two
+    // halves, whose 32 tokens stream all of W2); up to half: 64; beyond that a full-length item
+    // is no longer (1024 tokens, H = 1024: 48 misses, half a round over, 138 us either way).
+    // Measured without and with: 33 misses 125 -> 110 us, 40 (64 items over) 129 -> 121,
+    // 232 (64 over) 595 -> 560; 256 tokens, H = 512: 160 misses 56 -> 47; 768 tokens, H = 2048:
+    // 12 misses 137 -> 118, 16 146 -> 136. A handle held to split outputs keeps whole rounds.
+    int full = units, cut = 0;
+    if (TOK == kTokMax && d.eps_mode != nullptr && units > G) {
+        const int rest = units % G;
+        if (rest > 0) cut = (NS == 2 && whole ? 16 * rest <= 3 * G : 4 * rest <= G) ? 4 : (2 * rest <= G ? 2 : 0);
+        if (cut) full = units - rest;
+    }
+    for (int item = blockIdx.x; item < full; item += G) {
         const int tbk = whole ? item : item / NS;
         for (int q = 0; q < per; ++q) half(tbk / nblk, tbk % nblk, whole ? q : item % NS, whole);
+    }
+    if constexpr (TOK == kTokMax) if (cut) {
+        __syncthreads();                     // the reduction buffer is read
+        auto take = [&](auto ts_c, auto whole_c) {
+            constexpr int TS = decltype(ts_c)::value, C = 4 / TS;   // items per 128 tokens
+            constexpr bool WH = decltype(whole_c)::value;
+            fine_items<H, TS, kNH, (!WH && TS == 2 && H > 1024 ? 2 : 1), WH>(
+                d, &h1s[0][0], xs, es, mpre, fmiss, fnewest, (units - full) * C, [=](int i) {
+                    const int u = full + i / C, tbk = WH ? u : u / NS;
+                    return FineItem{tbk / nblk, tbk % nblk * C + i % C, WH ? 0 : u % NS};
+                });
+        };
+        typedef std::integral_constant<int, 1> c1;
+        typedef std::integral_constant<int, 2> c2;
+        if constexpr (NS <= 2) {
+            if (whole) {
+                if (cut == 4) take(c1{}, std::true_type{});
+                else take(c2{}, std::true_type{});
+                return;
+            }
+        }
+        if (cut == 4) take(c1{}, std::false_type{});
+        else take(c2{}, std::false_type{});
     }
 }
 
