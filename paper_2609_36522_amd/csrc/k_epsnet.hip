@@ -607,6 +607,11 @@ __global__ __launch_bounds__(kWaves * 64) void k_eps_mlp(Dev d) {
             w1a = *reinterpret_cast<const bf16x8*>(d.w1t + (size_t)(n0 + l32) * kFeat + g * 8);
             ek = es + n0 + g * 4;
         };
+        // The W1 fragment of a chunk is loaded while the chunk before the last computes its h1, so
+        // that the first GEMM1 of a chunk does not wait for a load younger than the W2 fragments
+        // in flight (and so for those too). At H = 2048 it is slower (21 misses of 768 tokens:
+        // 150 -> 153 us).
+        constexpr bool kW1Ahead = H <= 1024;
         f32x16 h1acc;
         // The accumulator starts at e_t (row = unit), so the MFMA returns x W1 + e_t; the
         // GELU slices store 2 h1 (W2 is stored halved, see gelu2_erf).
@@ -665,41 +670,51 @@ __global__ __launch_bounds__(kWaves * 64) void k_eps_mlp(Dev d) {
                         w2r, lane * 16, sb + (hb * KS + j) * 64 * 16, 0));
         };
         bf16x8 A0[2][2], A1[2][2];
-        // GEMM2 MFMA group of k-block kb: 16 MFMAs over the four 32-token slices; the B
-        // operands (h1^T from LDS) of slice tb4 + 1 are read while slice tb4 multiplies.
-        auto mma = [&](const bf16x8 (&A)[2][2], const __bf16* h1b, int kb) {
-            bf16x8 B[2][2];
+        // GEMM2 step st = (k-block kb, 32-token slice): four MFMAs. The B operands (h1^T from LDS)
+        // of the next step, also across k-blocks, are read before them; the scheduling barriers
+        // keep the reads there (the compiler otherwise moves each right before its use, and every
+        // four MFMAs wait for a round trip to LDS). A wave's cycles per chunk with GELU work fell
+        // by 7%; the launch gains less, since with all CUs busy the clock gives (1.7 GHz): 29
+        // misses of 1024 tokens, H = 1024, 85 -> 83 us. Two steps ahead spills (15 registers).
+        constexpr int STEPS = KBC * TB4;
+        bf16x8 B[2][2];
+        auto load_b = [&](const __bf16* h1b, int st) {
+            const int kb = st / TB4, tb4 = st % TB4;
 #pragma unroll
-            for (int j = 0; j < 2; ++j) B[0][j] = *reinterpret_cast<const bf16x8*>(h1b + kb * 32 + j * 16);
+            for (int j = 0; j < 2; ++j)
+                B[st % 2][j] = *reinterpret_cast<const bf16x8*>(h1b + tb4 * 32 * HRow + kb * 32 + j * 16);
+        };
+        auto mma = [&](const bf16x8 (&A)[2][2], const __bf16* h1b, int kb) {
 #pragma unroll
             for (int tb4 = 0; tb4 < TB4; ++tb4) {
-                if (tb4 + 1 < TB4) {
-#pragma unroll
-                    for (int j = 0; j < 2; ++j)
-                        B[(tb4 + 1) & 1][j] = *reinterpret_cast<const bf16x8*>(
-                            h1b + (tb4 + 1) * 32 * HRow + kb * 32 + j * 16);
-                }
+                const int st = kb * TB4 + tb4;
+                if (st + 1 < STEPS) load_b(h1b, st + 1);
+                __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
                 for (int j = 0; j < 2; ++j)
 #pragma unroll
                     for (int hb = 0; hb < 2; ++hb)
-                        acc2[hb][tb4] = mfma32(A[hb][j], B[tb4 & 1][j], acc2[hb][tb4]);
+                        acc2[hb][tb4] = mfma32(A[hb][j], B[st % 2][j], acc2[hb][tb4]);
+                __builtin_amdgcn_sched_barrier(0);
             }
         };
         // One chunk of GEMM2 at position i of the half's chunk order (two register stages of
         // W2^T fragments, the stream running on across chunk boundaries); position i is in
         // buffer i & 1. MORE: a chunk follows; its h1 slices are computed between the MFMA
-        // groups (same basic block, so the VALU work of the GELU can be interleaved with the
-        // MFMAs). A wave raises its issue priority while it feeds MFMA groups, so that the two
+        // groups. A wave raises its issue priority while it feeds MFMA groups, so that the two
         // waves of a SIMD drift out of step (one in its MFMA group while the other is in its
         // GELU slice).
         auto chunk = [&](int i, auto more_c) {
             constexpr bool more = decltype(more_c)::value;
             const int kc = korder<KCH>(odd, i);
             const int kn = more ? korder<KCH>(odd, i + 1) : 0;
-            if constexpr (more) h1_setup(kn);
+            if constexpr (more) {
+                if constexpr (kW1Ahead) ek = es + kn * kKC + w * 32 + g * 4;
+                else h1_setup(kn);
+            }
             __bf16* nbuf = h1s[(i + 1) & 1];
             const __bf16* h1b = h1s[i & 1] + l32 * HRow + g * 8;
+            load_b(h1b, 0);
 #pragma unroll
             for (int it = 0; it < ITER; ++it) {
                 const int kb = 2 * it;
@@ -709,6 +724,10 @@ __global__ __launch_bounds__(kWaves * 64) void k_eps_mlp(Dev d) {
                 mma(A0, h1b, kb);
                 if constexpr (more) {
                     if (it < TB4) h1_slice(nbuf, kn, it);   // one 32-token slice per iteration
+                    if (kW1Ahead && it == TB4 - 1) {
+                        const int k2 = i + 2 < KCH ? korder<KCH>(odd, i + 2) : 0;
+                        w1a = *reinterpret_cast<const bf16x8*>(d.w1t + (size_t)(k2 * kKC + w * 32 + l32) * kFeat + g * 8);
+                    }
                 }
                 __builtin_amdgcn_sched_barrier(0);
                 __builtin_amdgcn_s_setprio(0);
@@ -725,6 +744,7 @@ __global__ __launch_bounds__(kWaves * 64) void k_eps_mlp(Dev d) {
             }
             __syncthreads();                 // chunk kc + 1 complete; chunk kc's buffer free
         };
+        if constexpr (kW1Ahead) h1_setup(korder<KCH>(odd, 1));
         load_a(A0, korder<KCH>(odd, 0), 0);
         for (int i = 0; i + 1 < KCH; ++i) chunk(i, std::true_type{});
         chunk(KCH - 1, std::false_type{});
