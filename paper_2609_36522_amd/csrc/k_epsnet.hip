@@ -42,6 +42,7 @@
 #include <hip/hip_ext.h>
 
 #include "pa_device.h"
+#include "pa_parareal.h"
 #include "pa_slide.h"
 
 namespace pa {
@@ -167,8 +168,8 @@ __device__ __forceinline__ void fine_items(const Dev& d, __bf16* h1, __bf16* xs,
         while (mpre[n + 1] <= gm) ++n;               // sample of list entry gm (uniform)
         const int jm = gm - mpre[n];
         const Ctrl* ctrl = d.ctrl + n;
-        const int t = d.fused_slide ? fmiss[jm] : ctrl->miss_idx[jm];
-        const int newest = d.fused_slide ? fnewest : ctrl->newest;
+        const int t = d.fused_slide ? fmiss[jm] : (d.pr_dev ? fmiss[n] : ctrl->miss_idx[jm]);
+        const int newest = d.fused_slide ? fnewest : (d.pr_dev ? t : ctrl->newest);
         const int ns0 = WHOLE ? 0 : it.ug * UF / kNH;
         const int ub00 = it.ug * UB + (UB == 4 ? (w & 3) : w * UBW);   // this wave's first unit block
 
@@ -497,9 +498,36 @@ __global__ __launch_bounds__(kWaves * 64) void k_eps_mlp(Dev d) {
                 fnewest = c->newest;
             }
         }
-    } else if (w == 0) {
+    } else {
+        // Parareal: every block computes the hit test of the launch's requests from the partial
+        // sums of their deviations, wave by wave (block 0 publishes it); a block of the sampler
+        // has at most one miss, at timestep fmiss[block].
+        static_assert(PA_PR_MAX_BLOCKS <= PA_MAX_WINDOW, "one timestep per Parareal block");
+        if (d.pr_dev) {
+            for (int n = w; n < d.N; n += kWaves) {
+                int t = 0;
+                const bool act = pr_request(d.pr, n, &t) && !d.pr.pc->done;
+                double dev = __builtin_nan("");
+                if (act && d.valid[t]) {
+                    double acc = 0.0;
+                    for (int q = lane; q < d.pr.nchunk; q += 64) acc += d.pr_dev[(size_t)n * d.pr.nchunk + q];
+                    dev = wave_sum(acc) / (double)d.D;
+                }
+                const bool hit = dev < d.delta;      // strict: delta == 0 never hits
+                if (lane == 0) {
+                    fmiss[n] = act && !hit ? t : -1;
+                    if (blockIdx.x == 0) {
+                        if (act) pr_publish(d, d.pr, n, t, hit, dev);
+                        else d.ctrl[n].m = 0;
+                    }
+                }
+            }
+            __syncthreads();
+        }
+    }
+    if (!d.fused_slide && w == 0) {
         int v = 0;
-        if (lane < d.N) v = d.ctrl[lane].done ? 0 : d.ctrl[lane].m;
+        if (lane < d.N) v = d.pr_dev ? fmiss[lane] >= 0 : (d.ctrl[lane].done ? 0 : d.ctrl[lane].m);
 #pragma unroll
         for (int off = 1; off < 64; off <<= 1) {
             const int u = __shfl_up(v, off, 64);
@@ -563,8 +591,8 @@ __global__ __launch_bounds__(kWaves * 64) void k_eps_mlp(Dev d) {
         while (mpre[n + 1] <= gm) ++n;               // sample of list entry gm (uniform)
         const int jm = gm - mpre[n];
         const Ctrl* ctrl = d.ctrl + n;
-        const int t = d.fused_slide ? fmiss[jm] : ctrl->miss_idx[jm];
-        const int newest = d.fused_slide ? fnewest : ctrl->newest;
+        const int t = d.fused_slide ? fmiss[jm] : (d.pr_dev ? fmiss[n] : ctrl->miss_idx[jm]);
+        const int newest = d.fused_slide ? fnewest : (d.pr_dev ? t : ctrl->newest);
         const int hb0 = ns * (kNH / 32) + w * 2;   // this wave's first 32-unit block of W2^T
 
         const int odd = ns & 1;

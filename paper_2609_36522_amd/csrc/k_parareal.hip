@@ -9,7 +9,11 @@
 // the output U_B. Xh/Eh/valid are the timestep cache [T][D]. Per request:
 //   k_pr_test          Eq. (4)-(5) hit test of the request's input against the cache entry
 //                      of its timestep (one block per Parareal block, fp64 fixed-order sum);
-//   k_eps_mlp          the network on the misses;
+//                      linear network only;
+//   k_eps_mlp          the same test from partial sums that the kernel which wrote the input left
+//                      (every block computes it, block 0 publishes it), then the network on the
+//                      misses; a launch of its own for the test took 4.0 us (4x32x32) to 6.3 us
+//                      (4x96x96) per request;
 //   k_pr_fine_step     Eq. (6)-(7) assembly and cache update, then one fine DDIM step;
 //   k_pr_coarse        Eq. (6)-(7), then the coarse step and the Parareal correction
 //                      U_{n+1} <- G_n(U_n) + (F_n - G_n^old), or the copy U_{k+1} <- F_k,
@@ -83,14 +87,26 @@ __device__ __forceinline__ float4 ddim_step(float4 x, float4 e, double a, double
 
 }  // namespace
 
-// Which request, if any, Parareal block n makes in this launch (uniform per block).
-__device__ __forceinline__ bool pr_request(const PrArgs& a, int n, int* t) {
-    if (a.mode == PR_FINE) {
-        *t = n * a.L + a.j;
-        return n >= a.k;
-    }
-    *t = n * a.L;
-    return n == a.n;
+// Sum over the kStepThreads threads of a block in a fixed order; valid in thread 0. The block
+// may call it again only after a barrier.
+__device__ __forceinline__ double block_sum_step(double v, double* sh) {
+    v = wave_sum(v);
+    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
+    __syncthreads();
+    double s = 0.0;
+    if (threadIdx.x == 0)
+        for (int w = 0; w < kStepThreads / 64; ++w) s += sh[w];
+    return s;
+}
+
+__device__ __forceinline__ double abs_dev(float4 a, float4 b) {
+    return (fabs((double)a.x - (double)b.x) + fabs((double)a.y - (double)b.y)) +
+           (fabs((double)a.z - (double)b.z) + fabs((double)a.w - (double)b.w));
+}
+
+__device__ __forceinline__ double sq_dev(float4 a, float4 b) {
+    const double dx = (double)a.x - b.x, dy = (double)a.y - b.y, dz = (double)a.z - b.z, dw = (double)a.w - b.w;
+    return (dx * dx + dy * dy) + (dz * dz + dw * dw);
 }
 
 __global__ __launch_bounds__(kTestThreads) void k_pr_test(Dev d, PrArgs a) {
@@ -113,44 +129,35 @@ __global__ __launch_bounds__(kTestThreads) void k_pr_test(Dev d, PrArgs a) {
         double acc = 0.0;
         for (int i = threadIdx.x; i < d.D / 4; i += kTestThreads) {
             const float4 u = x4[i], v = h4[i];
-            acc += (fabs((double)u.x - (double)v.x) + fabs((double)u.y - (double)v.y)) +
-                   (fabs((double)u.z - (double)v.z) + fabs((double)u.w - (double)v.w));
+            acc += abs_dev(u, v);
         }
         dev = block_sum_1024(acc, sh) / (double)d.D;
     }
     if (threadIdx.x == 0) {
         const bool hit = entry && dev < d.delta;    // strict: delta == 0 never hits
-        c->m = hit ? 0 : 1;
-        c->miss_idx[0] = t;
-        c->newest = t;
-        c->done = 0;
-        c->slot_miss[0] = hit ? 0 : 1;
-        if (hit) c->hits += 1;
-        else c->nfe += 1;
-        if (d.trace_pr) {
-            pa_request_trace_t* r = d.trace_pr + a.rec + (a.mode == PR_FINE ? n - a.k : 0);
-            r->iteration = a.mode == PR_INIT ? -1 : a.k;
-            r->phase = a.mode;
-            r->t = t;
-            r->block = n;
-            r->hit = hit ? 1 : 0;
-            r->dev = dev;
-        }
+        pr_publish(d, a, n, t, hit, dev);
     }
 }
 
-// One fine step of every active block: Eq. (6)-(7) for its request, then the DDIM step.
+// One fine step of every active block: Eq. (6)-(7) for its request, then the DDIM step, and the
+// partial sums of the next request's Eq. (4) deviation. The last fine step of block k (of two or
+// more) also is the copy U_{k+1} <- F_k.
 __global__ __launch_bounds__(kStepThreads) void k_pr_fine_step(Dev d, PrArgs a) {
     const int n = blockIdx.y;
     int t = 0;
     if (!pr_request(a, n, &t) || a.pc->done) return;
     const Ctrl* c = d.ctrl + n;
     const int c4 = blockIdx.x * kStepThreads + threadIdx.x;
+    const size_t D = (size_t)d.D, rows = (size_t)d.T + 1;
     const bool miss = c->slot_miss[0] != 0;
+    const bool last = a.j == a.L - 1, copy = last && a.L > 1 && n == a.k;
+    const int tn = t + 1;                             // the next request's timestep
+    const bool test = d.pr_dev && (copy ? tn < d.T : !last) && d.valid[tn] != 0;
+    double dev = 0.0, res = 0.0;
     if (c4 < d.D / 4) {
-        const size_t D = (size_t)d.D;
-        float* xr = d.X + ((size_t)n * (d.T + 1) + t) * D;
+        float* xr = d.X + ((size_t)n * rows + (size_t)t) * D;
         const float4 x = reinterpret_cast<const float4*>(xr)[c4];
+        const float4 xh = test ? reinterpret_cast<const float4*>(d.Xh + (size_t)tn * D)[c4] : x;
         float4 e;
         if (miss) {
             e = f4_fresh(d, n, c4, t, x);
@@ -160,12 +167,31 @@ __global__ __launch_bounds__(kStepThreads) void k_pr_fine_step(Dev d, PrArgs a) 
         } else {
             e = reinterpret_cast<const float4*>(d.Eh + (size_t)t * D)[c4];
         }
-        reinterpret_cast<float4*>(xr + D)[c4] = ddim_step(x, e, d.coef[3 * t], d.coef[3 * t + 1]);
+        const float4 y = ddim_step(x, e, d.coef[3 * t], d.coef[3 * t + 1]);
+        reinterpret_cast<float4*>(xr + D)[c4] = y;
+        if (test) dev = abs_dev(y, xh);
+        if (copy) {
+            float4* u = reinterpret_cast<float4*>(d.X + ((size_t)(n + 1) * rows + (size_t)tn) * D) + c4;
+            res = sq_dev(y, *u);
+            *u = y;
+        }
     }
     if (miss && blockIdx.x == 0 && threadIdx.x == 0) d.valid[t] = 1;
+    __shared__ double sh[2][kStepThreads / 64];
+    if (test) {                                       // uniform over the block
+        const double s = block_sum_step(dev, sh[0]);
+        if (threadIdx.x == 0) d.pr_dev[(size_t)(copy ? n + 1 : n) * gridDim.x + blockIdx.x] = s;
+    }
+    if (copy) {
+        const double s = block_sum_step(res, sh[1]);
+        if (threadIdx.x == 0) d.part_res[(size_t)(n + 1) * gridDim.x + blockIdx.x] = s;
+    }
 }
 
-// Coarse request of block a.n (PR_INIT / PR_COARSE), or the copy U_{k+1} <- F_k (PR_COPY).
+// Coarse request of block a.n (PR_INIT / PR_COARSE), or the copy U_{k+1} <- F_k (PR_COPY), and
+// the partial sums of two later Eq. (4) deviations: of U_{n+1} from its entry, and of U_n, the
+// input of block n's first fine step too, from the entry this request leaves (the request's own
+// deviation on a hit; of the input from itself on a miss).
 __global__ __launch_bounds__(kStepThreads) void k_pr_coarse(Dev d, PrArgs a) {
     if (a.pc->done) return;
     const int n = a.n, L = a.L;
@@ -174,20 +200,18 @@ __global__ __launch_bounds__(kStepThreads) void k_pr_coarse(Dev d, PrArgs a) {
     const bool ok = c4 < d.D / 4;
     float* unext = d.X + ((size_t)(n + 1) * rows + (size_t)(n + 1) * L) * D;   // U_{n+1}
     const float* fn = d.X + ((size_t)n * rows + (size_t)(n + 1) * L) * D;      // F_n
-    double part = 0.0;
-    if (a.mode == PR_COPY) {
-        if (ok) {
-            const float4 f = reinterpret_cast<const float4*>(fn)[c4];
-            const float4 o = reinterpret_cast<const float4*>(unext)[c4];
-            reinterpret_cast<float4*>(unext)[c4] = f;
-            const double dx = (double)f.x - o.x, dy = (double)f.y - o.y, dz = (double)f.z - o.z, dw = (double)f.w - o.w;
-            part = (dx * dx + dy * dy) + (dz * dz + dw * dw);
-        }
-    } else {
-        const int t = n * L;
-        const Ctrl* c = d.ctrl + n;
-        const bool miss = c->slot_miss[0] != 0;
-        if (ok) {
+    const int tn = (n + 1) * L;
+    const bool test = d.pr_dev && tn < d.T && d.valid[tn] != 0;
+    const bool miss = a.mode != PR_COPY && d.ctrl[n].slot_miss[0] != 0;
+    double part = 0.0, dev = 0.0, self = 0.0;
+    if (ok) {
+        const float4 xh = test ? reinterpret_cast<const float4*>(d.Xh + (size_t)tn * D)[c4] : make_float4(0.f, 0.f, 0.f, 0.f);
+        float4 un;
+        if (a.mode == PR_COPY) {
+            un = reinterpret_cast<const float4*>(fn)[c4];
+            part = sq_dev(un, reinterpret_cast<const float4*>(unext)[c4]);
+        } else {
+            const int t = n * L;
             const float* u = d.X + ((size_t)n * rows + (size_t)t) * D;
             const float4 x = reinterpret_cast<const float4*>(u)[c4];
             float4 e;
@@ -196,12 +220,13 @@ __global__ __launch_bounds__(kStepThreads) void k_pr_coarse(Dev d, PrArgs a) {
                 reinterpret_cast<float4*>(d.Eh + (size_t)t * D)[c4] = e;
                 reinterpret_cast<float4*>(d.Xh + (size_t)t * D)[c4] = x;
                 if (d.trace_eps) reinterpret_cast<float4*>(d.trace_eps + (size_t)a.rec * D)[c4] = e;
+                self = abs_dev(x, x);                 // 0, or NaN from a non-finite input
             } else {
                 e = reinterpret_cast<const float4*>(d.Eh + (size_t)t * D)[c4];
             }
             const float4 g = ddim_step(x, e, d.pr_coef[2 * n], d.pr_coef[2 * n + 1]);
             float4* gst = reinterpret_cast<float4*>(d.Gc + (size_t)n * D) + c4;
-            float4 un = g;
+            un = g;
             if (a.mode == PR_COARSE) {
                 const float4 f = reinterpret_cast<const float4*>(fn)[c4];
                 const float4 go = *gst;
@@ -209,26 +234,26 @@ __global__ __launch_bounds__(kStepThreads) void k_pr_coarse(Dev d, PrArgs a) {
                                  (float)((double)g.y + ((double)f.y - (double)go.y)),
                                  (float)((double)g.z + ((double)f.z - (double)go.z)),
                                  (float)((double)g.w + ((double)f.w - (double)go.w)));
-                const float4 o = reinterpret_cast<const float4*>(unext)[c4];
-                const double dx = (double)un.x - o.x, dy = (double)un.y - o.y;
-                const double dz = (double)un.z - o.z, dw = (double)un.w - o.w;
-                part = (dx * dx + dy * dy) + (dz * dz + dw * dw);
+                part = sq_dev(un, reinterpret_cast<const float4*>(unext)[c4]);
             }
             *gst = g;
-            reinterpret_cast<float4*>(unext)[c4] = un;
         }
-        if (miss && blockIdx.x == 0 && threadIdx.x == 0) d.valid[t] = 1;
+        reinterpret_cast<float4*>(unext)[c4] = un;
+        if (test) dev = abs_dev(un, xh);
     }
+    if (miss && blockIdx.x == 0 && threadIdx.x == 0) d.valid[n * L] = 1;
+    __shared__ double sh[3][kStepThreads / 64];
     if (a.mode != PR_INIT) {
-        __shared__ double sh[kStepThreads / 64];
-        part = wave_sum(part);
-        if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = part;
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            double s = 0.0;
-            for (int w = 0; w < kStepThreads / 64; ++w) s += sh[w];
-            d.part_res[(size_t)(n + 1) * gridDim.x + blockIdx.x] = s;
-        }
+        const double s = block_sum_step(part, sh[0]);
+        if (threadIdx.x == 0) d.part_res[(size_t)(n + 1) * gridDim.x + blockIdx.x] = s;
+    }
+    if (test) {
+        const double s = block_sum_step(dev, sh[1]);
+        if (threadIdx.x == 0) d.pr_dev[(size_t)(n + 1) * gridDim.x + blockIdx.x] = s;
+    }
+    if (miss && d.pr_dev) {
+        const double s = block_sum_step(self, sh[2]);
+        if (threadIdx.x == 0) d.pr_dev[(size_t)n * gridDim.x + blockIdx.x] = s;
     }
 }
 

@@ -44,6 +44,20 @@ enum EpsMode : int32_t {
 };
 constexpr int kFineGroups = 8;  // 64-unit partial outputs per half
 
+struct PrCtrl;
+
+// The requests a Parareal launch serves (see pa_parareal.h).
+struct PrArgs {
+    int32_t mode;       // PrMode
+    int32_t L;          // fine steps per block
+    int32_t k;          // iteration (fine: blocks n >= k are active)
+    int32_t j;          // fine step within the block
+    int32_t n;          // block of a coarse request or copy
+    int32_t rec;        // trace record index of the launch's first request
+    int32_t nchunk;     // partial sums per boundary and per request
+    PrCtrl* pc;
+};
+
 // Geometry and device buffers handed to every kernel launcher. Per-sample buffers are
 // stacked along a leading sample index n < N.
 struct Dev {
@@ -85,6 +99,10 @@ struct Dev {
     int32_t picard_blocks;
     int32_t mlp_grid;
     // Parareal sampler only (k_parareal.hip)
+    double* pr_dev;                    // [B][chunks] partial sums of the Eq. (4) deviation of each
+                                       // block's next request, left by the kernel that wrote its
+                                       // input; null: k_pr_test computes the deviations
+    PrArgs pr;                         // requests whose hit tests the network launch computes
     float* Gc;                         // [B][D] stored coarse values G_n
     double* pr_coef;                   // [B][2] coarse step (ac_n, bc_n)
     pa_request_trace_t* trace_pr;      // request records or null

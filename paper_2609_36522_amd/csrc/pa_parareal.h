@@ -16,17 +16,37 @@ struct alignas(64) PrCtrl {
 enum PrMode : int32_t { PR_INIT = 0, PR_FINE = 1, PR_COARSE = 2, PR_COPY = 3 };
 enum PrKernel : int32_t { PRK_RESET, PRK_TEST, PRK_FINE, PRK_COARSE, PRK_CHECK };
 
-// Per-launch arguments: which requests this launch serves.
-struct PrArgs {
-    int32_t mode;       // PrMode
-    int32_t L;          // fine steps per block
-    int32_t k;          // iteration (fine: blocks n >= k are active)
-    int32_t j;          // fine step within the block
-    int32_t n;          // block of a coarse request or copy
-    int32_t rec;        // trace record index of the launch's first request
-    int32_t nchunk;     // residual partials per boundary
-    PrCtrl* pc;
-};
+// Which request, if any, Parareal block n makes in this launch (uniform per block).
+__device__ __forceinline__ bool pr_request(const PrArgs& a, int n, int* t) {
+    if (a.mode == PR_FINE) {
+        *t = n * a.L + a.j;
+        return n >= a.k;
+    }
+    *t = n * a.L;
+    return n == a.n;
+}
+
+// Outcome of block n's request at timestep t with Eq. (4) deviation dev (NaN without an entry),
+// for the step kernel of the request, the counters and the trace. One thread per block.
+__device__ __forceinline__ void pr_publish(const Dev& d, const PrArgs& a, int n, int t, bool hit, double dev) {
+    Ctrl* c = d.ctrl + n;
+    c->m = hit ? 0 : 1;
+    c->miss_idx[0] = t;
+    c->newest = t;
+    c->done = 0;
+    c->slot_miss[0] = hit ? 0 : 1;
+    if (hit) c->hits += 1;
+    else c->nfe += 1;
+    if (d.trace_pr) {
+        pa_request_trace_t* r = d.trace_pr + a.rec + (a.mode == PR_FINE ? n - a.k : 0);
+        r->iteration = a.mode == PR_INIT ? -1 : a.k;
+        r->phase = a.mode;
+        r->t = t;
+        r->block = n;
+        r->hit = hit ? 1 : 0;
+        r->dev = dev;
+    }
+}
 
 hipError_t launch_pr(const Dev& d, const PrArgs& a, int kernel, hipStream_t st);
 int pr_chunks(int D);

@@ -55,9 +55,10 @@ struct paraanya_parareal {
         return a;
     }
 
-    // One batch of requests: hit test, network on the misses, then the step kernel.
+    // One batch of requests: hit test and network on the misses, then the step kernel.
     int request(const PrArgs& a, int step_kernel) {
-        PA_HIP(pa::launch_pr(d, a, pa::PRK_TEST, stream));
+        d.pr = a;                     // the network launch computes the hit tests (pr_dev)
+        if (!d.pr_dev) PA_HIP(pa::launch_pr(d, a, pa::PRK_TEST, stream));
         if (model == PA_EPS_PATCH_MLP) {
             hipEvent_t e0 = nullptr, e1 = nullptr;
             if (flags & PA_FLAG_PROFILE) {
@@ -178,8 +179,10 @@ int paraanya_parareal_create(const int32_t latent_shape[4], int32_t T, const pa_
     if (he != hipSuccess) return bail(hip_fail(he, "hipMemcpyAsync(pr_coef)"));
     he = hipMemsetAsync(d.ctrl, 0, Bz * sizeof(Ctrl), h->stream);
     if (he != hipSuccess) return bail(hip_fail(he, "hipMemsetAsync(ctrl)"));
-    if (h->model == PA_EPS_PATCH_MLP)
+    if (h->model == PA_EPS_PATCH_MLP) {
         if ((rc = m.alloc(&d.eps_mode, 1 + Bz, "eps_mode"))) return bail(rc);
+        if ((rc = m.alloc(&d.pr_dev, Bz * h->nchunk, "pr_dev"))) return bail(rc);
+    }
     if ((rc = pa::setup_network(d, m, eps_model, tv.data(), cus, Bz, h->stream))) return bail(rc);
     // The host vectors above die at return: wait for the copies that read them.
     he = hipStreamSynchronize(h->stream);
@@ -207,7 +210,9 @@ int paraanya_parareal_sample(paraanya_parareal_t* h, const float* x_init, float*
             if ((rc = h->request(h->args(pa::PR_FINE, k, j, 0, rec), pa::PRK_FINE))) return rc;
             rec += B - k;
         }
-        PA_HIP(pa::launch_pr(d, h->args(pa::PR_COPY, k, 0, k, rec), pa::PRK_COARSE, h->stream));
+        // With one fine step per block the copy cannot be part of it: the next block's step
+        // reads U_{k+1} in the same launch.
+        if (L == 1) PA_HIP(pa::launch_pr(d, h->args(pa::PR_COPY, k, 0, k, rec), pa::PRK_COARSE, h->stream));
         for (int n = k + 1; n < B; ++n, ++rec)
             if ((rc = h->request(h->args(pa::PR_COARSE, k, 0, n, rec), pa::PRK_COARSE))) return rc;
         PA_HIP(pa::launch_pr(d, h->args(pa::PR_COARSE, k, 0, 0, rec), pa::PRK_CHECK, h->stream));

@@ -191,3 +191,25 @@ def test_parareal_repeated_samples_are_bitwise_identical(gpu_lib):
             stats.append(s.stats())
     assert all(np.array_equal(o, outs[0]) for o in outs)
     assert all(st == stats[0] for st in stats)
+
+
+# One fine step per block (the copy is a launch of its own), one block, two fine steps per block.
+@pytest.mark.parametrize("T,Bk", [(6, 6), (5, 1), (8, 4)])
+def test_parareal_short_blocks_mlp(T, Bk, gpu_lib):
+    test_parareal_parity(f"mlp_T{T}_B{Bk}", _wl(f"mlp_4x16x32_T{T}_B{Bk}", (4, 16, 32), T, Bk, "patch_mlp", 512),
+                         0.05, gpu_lib)
+
+
+@pytest.mark.parametrize("Bk", [1, 4])
+def test_parareal_nonfinite_input_never_hits(Bk, gpu_lib):
+    """A NaN deviation is a miss, also where the request's entry holds that very input."""
+    wl = _wl("mlp_nan", (4, 16, 32), 8, Bk, "patch_mlp", 512)
+    x = inputs.x_init(wl.latent).reshape(-1)
+    x[5] = np.nan
+    with B.parareal_from_workload(wl, 0.05, trace=True) as s:
+        with pytest.raises(B.PAError) as ei:
+            s.sample(torch.from_numpy(x).cuda())
+        assert ei.value.code == B.PA_ERR_NONFINITE
+        st = s.stats()
+        assert st["hits"] == 0 and st["nfe"] == st["requests"]
+        assert all(not s.trace(i)[0]["hit"] for i in range(st["requests"]))
