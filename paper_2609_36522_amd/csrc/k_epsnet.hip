@@ -148,10 +148,12 @@ __device__ __forceinline__ void fine_items(const Dev& d, __bf16* h1, __bf16* xs,
     constexpr int UB = UF / 32;                      // 32-unit blocks per item
     constexpr bool kSplitTok = UB == 4 && TS > 1;    // two wave groups, each half of the token slices
     constexpr int SL = kSplitTok ? TS / 2 : TS;      // token slices per wave
-    constexpr int DEPTH = UBW == 2 ? 8 : 16;         // k-steps of W2^T fragments in flight
+    // k-steps of W2^T fragments in flight: half of K at UBW = 1 (one wave's 32 KB at H = 1024; 16
+    // steps leave the stream waiting for round trips, 50 serial steps 882 against 866 us).
+    constexpr int DEPTH = UBW == 2 ? 8 : (H == 512 ? 16 : 32);
     constexpr int KCP = KCH / KP;                    // K-chunks (and h1 unit blocks per wave) per pass
     static_assert(UF == 128 || UF == 256 || UF == 512, "whole GEMM3 chains (64 units)");
-    static_assert(KS % DEPTH == 0 && 16 % DEPTH == 0, "a fragment group stays within a K-chunk");
+    static_assert(KS / KP % DEPTH == 0, "whole fragment groups");
     const int tid = threadIdx.x, lane = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int g = lane >> 5, l32 = lane & 31;
@@ -222,13 +224,15 @@ __device__ __forceinline__ void fine_items(const Dev& d, __bf16* h1, __bf16* xs,
         // DEPTH k-steps from k-step i0 of the half's order; reloads the stages if more follow.
         constexpr int KSP = KS / KP;                 // k-steps per pass
         auto steps = [&](int hf, int i0, auto more_c) {
-            const int p0 = KP == 1 ? korder<KCH>((ns0 + hf) & 1, i0 / 16) * kKC + (i0 % 16) * 16 : i0 % KSP * 16;
+            int p0 = 0;                              // h1 place of k-step i0 + j, less 16 j % 16
 #pragma unroll
             for (int j = 0; j < DEPTH; ++j) {
+                if (j % 16 == 0)
+                    p0 = KP == 1 ? korder<KCH>((ns0 + hf) & 1, (i0 + j) / 16) * kKC + i0 % 16 * 16 : (i0 + j) % KSP * 16;
                 bf16x8 B[SL];
 #pragma unroll
                 for (int sl = 0; sl < SL; ++sl)
-                    B[sl] = *reinterpret_cast<const bf16x8*>(hb + sl * 32 * HR + p0 + j * 16);
+                    B[sl] = *reinterpret_cast<const bf16x8*>(hb + sl * 32 * HR + p0 + j % 16 * 16);
 #pragma unroll
                 for (int sl = 0; sl < SL; ++sl)
 #pragma unroll
@@ -546,15 +550,15 @@ __global__ __launch_bounds__(kWaves * 64) void k_eps_mlp(Dev d) {
     // 15/16 x NS x the rounds of whole items do not exceed the rounds of half items spread
     // over all blocks: with one item per block when more than half of the blocks get one,
     // and always from about 7 rounds on.
-    const bool whole = d.whole_ok && NS <= 2 &&
-                       15 * NS * ((tblocks + G - 1) / G) <= 16 * ((tblocks * NS + G - 1) / G);
     const int fine = TOK == kTokMax && d.eps_mode != nullptr ? fine_choice<H>(mpre[d.N], d.ntok, d.fine_rows, G)
                                                              : FINE_NONE;
+    const bool whole = fine == FINE_NONE && d.whole_ok && NS <= 2 &&
+                       15 * NS * ((tblocks + G - 1) / G) <= 16 * ((tblocks * NS + G - 1) / G);
     if (d.eps_mode != nullptr && blockIdx.x == 0 && tid <= d.N)
         d.eps_mode[tid] = tid > 0 ? mpre[tid - 1]
                                   : (fine == FINE_32x128 || fine == FINE_32x256
                                          ? EPS_FINE
-                                         : (fine == FINE_NONE && whole ? EPS_WHOLE : EPS_SPLIT));
+                                         : (whole ? EPS_WHOLE : EPS_SPLIT));
     if constexpr (TOK == kTokMax) if (fine != FINE_NONE) {
         __bf16* hf = &h1s[0][0];
         // Unit groups fastest: with the blocks dealt to the XCDs in turn, an XCD's L2 fills with
@@ -582,7 +586,16 @@ __global__ __launch_bounds__(kWaves * 64) void k_eps_mlp(Dev d) {
         const_cast<__bf16*>(d.w2f), (short)0, H * H * 2, 0x00020000);
     const f32x16 zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f,
                            0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    float4 run = make_float4(0.f, 0.f, 0.f, 0.f);   // whole outputs: sum of the halves so far
+    // Whole outputs: each thread's sum of the halves so far, in LDS to keep four registers free.
+    // Whole outputs: each thread's sum of the halves so far. In LDS where there are two: four
+    // registers less across GEMM2, without which some were spilled, and a kernel with scratch
+    // memory takes longer to start as well (8 x 1024 tokens, H = 1024: 6755 -> 6707 us a sample).
+    float4* runs = nullptr;
+    if constexpr (NS == 2) {
+        __shared__ float4 runs_lds[NT];
+        runs = runs_lds;
+    }
+    float4 run = make_float4(0.f, 0.f, 0.f, 0.f);
     // One half (output units [512 ns, 512 ns + 512)) of the item (list entry gm, token block tb).
     // WHOLE: part of a whole-output block's item (ns > 0: the gather and the first h1 chunk of
     // the previous half are still in LDS).
@@ -829,8 +842,17 @@ __global__ __launch_bounds__(kWaves * 64) void k_eps_mlp(Dev d) {
                 sum.w += v.w;
             }
             if (whole_item) {
-                run = ns == 0 ? sum : make_float4(run.x + sum.x, run.y + sum.y, run.z + sum.z, run.w + sum.w);
-                sum = run;
+                if constexpr (NS == 2) {
+                    if (ns == 0) {
+                        runs[tid] = sum;
+                    } else {
+                        const float4 r = runs[tid];
+                        sum = make_float4(r.x + sum.x, r.y + sum.y, r.z + sum.z, r.w + sum.w);
+                    }
+                } else {
+                    run = ns == 0 ? sum : make_float4(run.x + sum.x, run.y + sum.y, run.z + sum.z, run.w + sum.w);
+                    sum = run;
+                }
             }
             if (!whole_item || ns == NS - 1) {
                 const int half_w = d.Wimg >> 1;
