@@ -1,6 +1,7 @@
 // Solver-side kernels of the sampler, for gfx950 (wave64). One sweep is
 //   [k_eps_mlp: network on the misses (patch-MLP only)] -> k_picard -> k_slide
-// and k_reset prepares the first window. Every kernel handles the N samples of a handle
+// (one patch-MLP sample: the slide runs in the next k_eps_mlp; few linear samples: in the next
+// k_picard) and k_reset prepares the first window. Every kernel handles the N samples of a handle
 // at once (grid dimension y of k_reset and k_picard, the blocks of k_slide); a sample that
 // is done makes its blocks exit at once.
 //   k_picard : Eq. (6) assembly (cached output for hits, fresh for misses: in the cache
@@ -101,6 +102,7 @@ __global__ void k_reset(Dev d) {
     }
     if (tid == 0) {
         if (d.pre) d.pre[n].pending = 0;
+        if (d.fused_linear) d.pre[d.N + n].pending = 0;
         c->s = 0;
         c->e = W;
         c->newest = 0;
@@ -165,17 +167,61 @@ __device__ __forceinline__ double4 d4_zero() { return make_double4(0.0, 0.0, 0.0
 // MINB: minimum blocks per CU the compiler must fit (1, or 6 (5 with step noise or one
 // partial output) for the 256-thread shape of batched handles: at most 76 (96) registers). NOISE: the step adds the
 // pre-drawn noise term (stochastic sampler).
-template <int COLS, int ROWS, int TPT, bool LINEAR, int NS, int MINB, bool NOISE>
+// FUSED (linear network): every block first computes the slide of the last sweep itself, from its
+// partials and snapshot (the other parity's, so no block reads what this launch writes); block 0
+// of a sample publishes it.
+template <int COLS, int ROWS, int TPT, bool LINEAR, int NS, int MINB, bool NOISE, bool FUSED = false>
 __global__ __launch_bounds__(COLS * ROWS, MINB) void k_picard(Dev d) {
     constexpr int kThr = COLS * ROWS;
     const int n = blockIdx.y;
     const Ctrl* ctrl = d.ctrl + n;
+    __shared__ uint8_t sm[PA_MAX_WINDOW + TPT + 1];
+    __shared__ uint8_t sr[PA_MAX_WINDOW + TPT];
+    static_assert(kThr >= PA_MAX_WINDOW, "one thread per window slot");
+    int s, e, newest;
+    if constexpr (FUSED) {
+        static_assert(LINEAR && ROWS * TPT <= kFusedLinearMaxWindow, "windows of this shape");
+        if (ctrl->done) return;
+        __shared__ SlideScratch sc;
+        __shared__ double sub[2 * ROWS * TPT * kSlideSubs];
+        Dev last = d;                       // the last sweep's partials
+        const size_t stride = (size_t)d.N * d.P * d.picard_blocks;
+        last.part_res += (d.parity ^ 1) * stride;
+        last.part_dev += (d.parity ^ 1) * stride;
+        d.part_res += d.parity * stride;
+        d.part_dev += d.parity * stride;
+        const SlidePre pre = d.pre[(d.parity ^ 1) * d.N + n];
+        slide_partials<kThr>(last, n, sub);
+        for (int j = threadIdx.x; j < PA_MAX_WINDOW + TPT; j += kThr) sm[j] = 0;
+        __syncthreads();
+        if (pre.pending) {
+            slide_core<kThr>(last, n, pre, blockIdx.x == 0, sc, sub);
+            if (sc.done) return;
+            s = sc.s2;
+            e = min(s + d.P, d.T);
+            newest = sc.newest;
+            for (int j = threadIdx.x; j < sc.m; j += kThr) {
+                sm[sc.miss_idx[j] - s] = 1;
+                sr[sc.miss_idx[j] - s] = (uint8_t)j;
+            }
+        } else {                            // first sweep after reset: the reset's window, all misses
+            s = ctrl->s;
+            e = ctrl->e;
+            newest = ctrl->newest;
+            for (int j = threadIdx.x; j < e - s; j += kThr) sm[j] = 1;
+        }
+    }
     // The network launch wrote the fresh outputs of the misses into Eh (whole outputs) rather
     // than split partials into Ep.
     const int mode = !LINEAR && d.eps_mode != nullptr ? *d.eps_mode : EPS_SPLIT;
     const bool whole = mode == EPS_WHOLE;
-    if (ctrl->done) return;
-    const int s = ctrl->s, e = ctrl->e, W = e - s, newest = ctrl->newest;
+    if constexpr (!FUSED) {
+        if (ctrl->done) return;
+        s = ctrl->s;
+        e = ctrl->e;
+        newest = ctrl->newest;
+    }
+    const int W = e - s;
     const int tid = threadIdx.x;
     const int col = tid % COLS, row = tid / COLS;
     const int n4 = d.D >> 2;
@@ -251,10 +297,7 @@ __global__ __launch_bounds__(COLS * ROWS, MINB) void k_picard(Dev d) {
             }
         }
     }
-    __shared__ uint8_t sm[PA_MAX_WINDOW + TPT + 1];
-    __shared__ uint8_t sr[PA_MAX_WINDOW + TPT];
-    static_assert(kThr >= PA_MAX_WINDOW, "one thread per window slot");
-    if (tid < W) {
+    if (!FUSED && tid < W) {
         sm[tid] = ctrl->slot_miss[tid];
         sr[tid] = ctrl->slot_rank[tid];
     }
@@ -380,10 +423,15 @@ __global__ __launch_bounds__(COLS * ROWS, MINB) void k_picard(Dev d) {
         const size_t pbase = (size_t)n * d.P * nblk;
         d.part_res[pbase + tid * nblk + blockIdx.x] = rres[tid];
         d.part_dev[pbase + tid * nblk + blockIdx.x] = rdev[tid];
-        if (blockIdx.x == 0 && ctrl->slot_miss[tid]) d.valid[(size_t)n * d.T + s + tid] = 1;   // Eq. (7) entry
+        if (blockIdx.x == 0 && (FUSED ? sm[tid] : ctrl->slot_miss[tid])) d.valid[(size_t)n * d.T + s + tid] = 1;   // Eq. (7) entry
     }
     // Fused sweep: the state this sweep started from, for the slide of the next network kernel.
-    if (d.fused_slide && blockIdx.x == 0 && tid == 0) d.pre[n] = slide_pre_of(*ctrl);
+    if constexpr (FUSED) {
+        // (Published by this block in slide_core, before several barriers; or by the reset.)
+        if (blockIdx.x == 0 && tid == 0) d.pre[d.parity * d.N + n] = slide_pre_of(*ctrl);
+    } else if (d.fused_slide && blockIdx.x == 0 && tid == 0) {
+        d.pre[n] = slide_pre_of(*ctrl);
+    }
 }
 
 template <bool LINEAR, int NS, bool NOISE>
@@ -396,6 +444,17 @@ static hipError_t launch_picard_t(const Dev& d, hipStream_t st, hipEvent_t e0, h
     // would otherwise spill) instead of four waves (one sample: within 2% either way, and the four-wave build is kept
     // there). With four partial outputs the register cap would spill.
     const bool occ = d.N >= 8;
+    if constexpr (LINEAR) {
+        if (d.fused_linear) {
+            switch (sh.rows * 4 + sh.tpt) {
+                case 16 * 4 + 1: hipExtLaunchKernelGGL((k_picard<16, 16, 1, LINEAR, NS, 1, NOISE, true>), grid, block, 0, st, e0, e1, 0, d); break;
+                case 16 * 4 + 2: hipExtLaunchKernelGGL((k_picard<16, 16, 2, LINEAR, NS, 1, NOISE, true>), grid, block, 0, st, e0, e1, 0, d); break;
+                case 32 * 4 + 2: hipExtLaunchKernelGGL((k_picard<16, 32, 2, LINEAR, NS, 1, NOISE, true>), grid, block, 0, st, e0, e1, 0, d); break;
+                default: return hipErrorInvalidValue;
+            }
+            return hipGetLastError();
+        }
+    }
     switch (sh.rows * 4 + sh.tpt) {
         case 16 * 4 + 1: hipExtLaunchKernelGGL((k_picard<16, 16, 1, LINEAR, NS, 1, NOISE>), grid, block, 0, st, e0, e1, 0, d); break;
         case 16 * 4 + 2:
@@ -440,6 +499,12 @@ __global__ __launch_bounds__(kSlideThreads) void k_slide(Dev d) {
     const Ctrl* ctrl = d.ctrl + n;
     __shared__ SlideScratch sc;
     __shared__ double sub[kSlideSubDoubles];
+    if (FROM_PRE && d.fused_linear) {            // the last enqueued sweep's partials and snapshot
+        const size_t stride = (size_t)d.N * d.P * d.picard_blocks;
+        d.part_res += d.parity * stride;
+        d.part_dev += d.parity * stride;
+        d.pre += d.parity * d.N;
+    }
     slide_partials<kSlideThreads>(d, n, sub);    // issued while the control block is read
     if (ctrl->done) return;
     SlidePre pre;

@@ -76,9 +76,13 @@ struct Dev {
     float* lin_c;              // [T]         linear network coefficients (or null)
     double* part_res;          // [N][P][picard_blocks] fp64 partial sums of Eq. (2) residuals
     double* part_dev;          // [N][P][picard_blocks] fp64 partial sums of Eq. (4) deviations
+                               // (both twice with fused_linear, by sweep parity)
     Ctrl* ctrl;                // [N]
-    SlidePre* pre;             // [N] pre-slide snapshots (fused sweep), or null
+    SlidePre* pre;             // [N] pre-slide snapshots (fused sweep; [2][N] with fused_linear)
     int32_t fused_slide;       // 1: the network kernel computes the slide (N = 1), no k_slide
+    int32_t fused_linear;      // 1: the Picard kernel of a linear network computes the last
+                               // sweep's slide itself, no k_slide
+    int32_t parity;            // fused_linear: of the sweep being enqueued
     uint64_t* progress;        // [N] host-mapped words: sweeps << 32 | done << 31 | nonfinite << 30 | s
     uint64_t* counters;        // [N][4] host-mapped final counters (epoch << 40 | value) or null
     uint32_t epoch;            // sample epoch of the counter words (24 bits, set at reset)
@@ -118,6 +122,14 @@ hipError_t launch_slide(const Dev& d, hipStream_t st, hipEvent_t start, hipEvent
 hipError_t launch_slide_pending(const Dev& d, hipStream_t st);
 // Largest fp64 partial-sum volume per sample the network kernel reduces redundantly per block.
 constexpr size_t kFusedSlideMaxBytes = 256 * 1024;
+// The same for the Picard kernel of a linear network, its longest window and the most blocks of a
+// launch (two per CU). Sample with a slide launch per sweep -> without (D, T, window, samples):
+// 256, 10, 4, 1 63 -> 46 us; 2220, 50, 17, 5 90 -> 75; 4096, 100, 32, 1 95 -> 85; 4096, 100, 32, 8
+// (512 blocks) 111 -> 100. More blocks repeat the slide more than they save: 4096, 100, 32, 32
+// (2048 blocks) 156 -> 190, 16384, 100, 8, 8 (2048) 254 -> 265.
+constexpr size_t kFusedLinearMaxBytes = 32 * 1024;
+constexpr int kFusedLinearMaxWindow = 64;
+constexpr long long kFusedLinearMaxBlocks = 512;
 hipError_t launch_picard(const Dev& d, hipStream_t st, int linear, hipEvent_t start, hipEvent_t stop);
 // single: the launch evaluates at most one latent.
 hipError_t launch_eps_mlp(const Dev& d, hipStream_t st, hipEvent_t start, hipEvent_t stop, int single = 0);

@@ -133,11 +133,12 @@ struct paraanya {
             if ((rc = timed(0, &e0, &e1))) return rc;
             PA_HIP(pa::launch_eps_mlp(d, stream, e0, e1));
         }
+        if (d.fused_linear) d.parity ^= 1;
         if ((rc = timed(1, &e0, &e1))) return rc;
         PA_HIP(pa::launch_picard(d, stream, model == PA_EPS_LINEAR, e0, e1));
-        if (d.fused_slide) {
-            // The slide runs at the start of the next network kernel (or of a finishing
-            // k_slide when the host needs the control block first).
+        if (d.fused_slide || d.fused_linear) {
+            // The slide runs at the start of the next network (or Picard) kernel, or of a
+            // finishing k_slide when the host needs the control block first.
             slide_pending = true;
             return PA_OK;
         }
@@ -217,14 +218,23 @@ int setup_handle(paraanya* h, const Request& q, const double* coef, const double
     if ((rc = h->alloc(&d.Eh, Nz * T * Dz, "Eh"))) return rc;
     if ((rc = h->alloc(&d.valid, Nz * T, "valid"))) return rc;
     if ((rc = h->alloc(&d.coef, 3 * T, "coef"))) return rc;
-    if ((rc = h->alloc(&d.part_res, Nz * P * d.picard_blocks, "part_res"))) return rc;
-    if ((rc = h->alloc(&d.part_dev, Nz * P * d.picard_blocks, "part_dev"))) return rc;
+    // Linear network, few partial sums: one launch per sweep, the Picard kernel starting with the
+    // last sweep's slide. Its partials and snapshots are kept twice, by sweep parity: the blocks
+    // of a launch read the last sweep's while others write their own. A workspace keeps the
+    // two-launch sweep and its smaller buffers (what fits it stays as it was).
+    const size_t part_bytes = 2 * P * d.picard_blocks * sizeof(double);
+    d.fused_linear = (q.em->kind == PA_EPS_LINEAR && !h->mem.ws && q.P <= pa::kFusedLinearMaxWindow &&
+                      part_bytes <= pa::kFusedLinearMaxBytes &&
+                      (long long)q.N * d.picard_blocks <= pa::kFusedLinearMaxBlocks) ? 1 : 0;
+    const size_t copies = d.fused_linear ? 2 : 1;
+    if ((rc = h->alloc(&d.part_res, copies * Nz * P * d.picard_blocks, "part_res"))) return rc;
+    if ((rc = h->alloc(&d.part_dev, copies * Nz * P * d.picard_blocks, "part_dev"))) return rc;
     if ((rc = h->alloc(&d.ctrl, Nz, "ctrl"))) return rc;
     // Fused sweep (network -> Picard, the slide computed by every block of the next network
     // kernel): one sample, patch-MLP, and a partial-sum volume that a block reduces quickly.
     d.fused_slide = (q.em->kind == PA_EPS_PATCH_MLP && q.N == 1 &&
-                     2 * P * d.picard_blocks * sizeof(double) <= pa::kFusedSlideMaxBytes) ? 1 : 0;
-    if ((rc = h->alloc(&d.pre, Nz, "pre"))) return rc;
+                     part_bytes <= pa::kFusedSlideMaxBytes) ? 1 : 0;
+    if ((rc = h->alloc(&d.pre, copies * Nz, "pre"))) return rc;
     if (h->flags & PA_FLAG_TRACE)
         if ((rc = h->alloc(&d.trace, Nz * T, "trace"))) return rc;
     if (q.eta > 0.0) {
@@ -357,13 +367,16 @@ int paraanya_sample(paraanya_t* h, const float* x_init, float* x_out) {
     // Launch loop without per-sweep synchronisation: the window slide (k_slide, or the next
     // network kernel in a fused sweep) publishes (completed sweeps, done, s) of every sample to
     // a pinned host word after each sweep; the host keeps enough sweeps in flight -- at least
-    // the kLookahead next ones and at least the ceil((T - s)/P) that the slowest sample
+    // the kLookahead next ones (see below) and at least the ceil((T - s)/P) that the slowest sample
     // certainly still needs (s advances by at most P per sweep) -- and stops enqueuing once
     // every sample is done. Sweeps enqueued after that exit at their first instruction. Every
     // sweep advances each unfinished sample's s by at least 1, so at most T sweeps are ever
     // enqueued (T + 1 for a fused sweep, see below). The stream is polled (at most once per
     // millisecond, see QueryPacer) while waiting, so a failed or idle stream ends the loop.
-    constexpr int kLookahead = 2;
+    // A linear network's fused sweep is one launch of a few microseconds, less than the time
+    // from the word to the next launch's start, so three are kept ahead (10-step sample 50 -> 46
+    // us; four 51: each launch after the last sweep costs about as much as it hides).
+    const int kLookahead = h->d.fused_linear ? 3 : 2;
     volatile uint64_t* prog = h->progress_host;
     auto scan = [&](int* completed, int* need) {      // returns true once all are done
         bool all = true;
@@ -380,9 +393,9 @@ int paraanya_sample(paraanya_t* h, const float* x_init, float* x_out) {
         }
         return all;
     };
-    // A fused sweep's slide runs in the next sweep's network kernel, so the sweep that finishes
-    // the sample is followed by one more (its network kernel only computes that slide).
-    const int cap = T + (h->d.fused_slide ? 1 : 0);
+    // A fused sweep's slide runs in the next sweep's first kernel, so the sweep that finishes
+    // the sample is followed by one more (that kernel only computes the slide).
+    const int cap = T + (h->d.fused_slide || h->d.fused_linear ? 1 : 0);
     int enqueued = 0;
     pa::QueryPacer pacer;
     for (unsigned spin = 0;; ++spin) {

@@ -336,6 +336,43 @@ def test_few_misses_equal_split_outputs(latent, hidden, P, batch, gpu_lib):
         assert np.array_equal(a, b)
 
 
+# Each window shape of the one-launch sweep; the batch just exceeds its most blocks.
+@pytest.mark.parametrize("latent,T,P,N,eta", [((4, 16, 16), 40, 12, 33, 0.5), ((3, 37, 20), 50, 17, 15, 0.0),
+                                              ((4, 32, 32), 40, 32, 9, 1.0), ((2, 32, 32), 90, 64, 17, 0.0),
+                                              ((2, 32, 32), 30, 1, 17, 0.0)])
+def test_linear_one_launch_sweep_equals_two(latent, T, P, N, eta, gpu_lib):
+    """A few linear samples run with one launch per sweep (the Picard kernel computes the last
+    sweep's slide), many with two: the same states, cache, counters and traces, bit for bit,
+    sampled twice in a row and swept one by one."""
+    c = inputs.linear_coefficients(T)
+    xb = torch.from_numpy(inputs.x_init_batch(latent, N)).cuda().reshape(N, -1)
+    z = torch.from_numpy(inputs.step_noise(N, T, xb.shape[1])).cuda()
+
+    def run(first, count, stepwise):
+        with B.Sampler(latent, T, P, 0.05, 1e-3, "linear", c=c, batch=count, eta=eta, trace=True) as s:
+            if eta:
+                s.set_noise(z[first:first + count].contiguous())
+            x = xb[first:first + count].contiguous()
+            if stepwise:
+                s.reset(x)
+                while not s.sweep(sync=True):
+                    pass
+            else:
+                s.sample(x)
+                s.sample(x)
+            return [(s.stats(n), s.traces(n), s.read_state(0, None, n)) for n in range(count)]
+
+    big = run(0, N, False)
+    for n, stepwise in ((0, False), (N - 1, False), (1, True)):
+        (st0, tr0, S0), (st1, tr1, S1) = big[n], run(n, 1, stepwise)[0]
+        assert st0 == st1 and len(tr0) == len(tr1)
+        for a, b in zip(tr0, tr1):
+            assert a["miss"] == b["miss"] and a["c"] == b["c"]
+            assert np.array_equal(a["dev"], b["dev"], equal_nan=True) and np.array_equal(a["r"], b["r"])
+        for A, Bv in zip(S0, S1):
+            assert np.array_equal(A, Bv)
+
+
 @pytest.mark.parametrize("wl,batch", [(W.TINY_LINEAR, 3), (W.SMALL_MLP, 1)], ids=["linear_batch3", "mlp"])
 def test_sample_output_alignment(wl, batch, gpu_lib):
     """Buffers at any 4-byte offset and an aliased x_init == x_out give the same final
