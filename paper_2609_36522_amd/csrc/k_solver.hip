@@ -420,9 +420,15 @@ __global__ __launch_bounds__(COLS * ROWS, MINB) void k_picard(Dev d) {
     __syncthreads();
     const int nblk = gridDim.x;
     if (tid < W) {
-        const size_t pbase = (size_t)n * d.P * nblk;
-        d.part_res[pbase + tid * nblk + blockIdx.x] = rres[tid];
-        d.part_dev[pbase + tid * nblk + blockIdx.x] = rdev[tid];
+        if (FUSED || d.fused_slide) {
+            const size_t pbase = (size_t)n * d.P * nblk;
+            d.part_res[pbase + tid * nblk + blockIdx.x] = rres[tid];
+            d.part_dev[pbase + tid * nblk + blockIdx.x] = rdev[tid];
+        } else {
+            double* part = d.part_rows + ((size_t)n * nblk + blockIdx.x) * 2 * d.P;
+            part[tid] = rres[tid];
+            part[d.P + tid] = rdev[tid];
+        }
         if (blockIdx.x == 0 && (FUSED ? sm[tid] : ctrl->slot_miss[tid])) d.valid[(size_t)n * d.T + s + tid] = 1;   // Eq. (7) entry
     }
     // Fused sweep: the state this sweep started from, for the slide of the next network kernel.
@@ -505,7 +511,8 @@ __global__ __launch_bounds__(kSlideThreads) void k_slide(Dev d) {
         d.part_dev += d.parity * stride;
         d.pre += d.parity * d.N;
     }
-    slide_partials<kSlideThreads>(d, n, sub);    // issued while the control block is read
+    if (d.part_rows) slide_partials_rows<kSlideThreads>(d, n, sub);   // issued while the control block is read
+    else slide_partials<kSlideThreads>(d, n, sub);
     if (ctrl->done) return;
     SlidePre pre;
     if (FROM_PRE) {

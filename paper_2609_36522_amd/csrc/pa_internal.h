@@ -112,6 +112,10 @@ struct Dev {
     pa_request_trace_t* trace_pr;      // request records or null
     float* trace_eps;                  // [records][D] fresh outputs of the misses, or null
     double* trace_res;                 // [B][B+1] boundary residuals per iteration, or null
+    // Solver kernels only
+    double* part_rows;                 // [N][picard_blocks][2P] part_res and part_dev with a Picard
+                                       // block's partials in a row, for the sweeps that k_slide
+                                       // ends (part_res and part_dev are then null), or null
 };
 
 // Kernel launchers (all asynchronous on `st`).

@@ -83,6 +83,33 @@ __device__ void slide_partials(const Dev& d, int n, double* sub) {
     }
 }
 
+// The same sub-sums from the row layout (part_rows): a Picard block's partials are contiguous, so
+// its stores fill whole lines of its own where slot by slot each was 8 bytes of a line shared with
+// 15 blocks on other XCDs (32 samples of 4x64x64, window 32, linear: Picard launch 43.7 -> 40.4
+// us, sample 397 -> 377), and a wave's load is one run. Only where k_slide reduces: in the network
+// kernel's prologue the slot layout is faster (one sample of 4x64x64, T = 100: 1024 against 1045 us).
+template <int NT>
+__device__ void slide_partials_rows(const Dev& d, int n, double* sub) {
+    const int nblk = d.picard_blocks, Q = 2 * d.P;
+    const double* part = d.part_rows + (size_t)n * nblk * Q;
+    const size_t stride = (size_t)kSlideSubs * Q;   // from a partial of a sub-sum to the next
+    for (int idx = threadIdx.x; idx < Q * kSlideSubs; idx += NT) {
+        const int u = idx / Q, q = idx - u * Q;
+        const double* pr = part + idx;              // partial u of reduction q
+        double acc = 0.0;
+        int b = u;
+        for (; b + (kSlideBatch - 1) * kSlideSubs < nblk; b += kSlideBatch * kSlideSubs, pr += kSlideBatch * stride) {
+            double v[kSlideBatch];
+#pragma unroll
+            for (int i = 0; i < kSlideBatch; ++i) v[i] = pr[i * stride];
+#pragma unroll
+            for (int i = 0; i < kSlideBatch; ++i) acc += v[i];
+        }
+        for (; b < nblk; b += kSlideSubs, pr += stride) acc += *pr;
+        sub[q * kSlideSubs + u] = acc;
+    }
+}
+
 // Progress word of sample n for the host's launch loop (pinned host memory, system scope):
 // completed sweeps << 32 | done << 31 | nonfinite << 30 | window start (at most T < 2^30).
 // The host reads the words, and the counter words of a done sample; anything else only after

@@ -227,13 +227,17 @@ int setup_handle(paraanya* h, const Request& q, const double* coef, const double
                       part_bytes <= pa::kFusedLinearMaxBytes &&
                       (long long)q.N * d.picard_blocks <= pa::kFusedLinearMaxBlocks) ? 1 : 0;
     const size_t copies = d.fused_linear ? 2 : 1;
-    if ((rc = h->alloc(&d.part_res, copies * Nz * P * d.picard_blocks, "part_res"))) return rc;
-    if ((rc = h->alloc(&d.part_dev, copies * Nz * P * d.picard_blocks, "part_dev"))) return rc;
     if ((rc = h->alloc(&d.ctrl, Nz, "ctrl"))) return rc;
     // Fused sweep (network -> Picard, the slide computed by every block of the next network
     // kernel): one sample, patch-MLP, and a partial-sum volume that a block reduces quickly.
     d.fused_slide = (q.em->kind == PA_EPS_PATCH_MLP && q.N == 1 &&
                      part_bytes <= pa::kFusedSlideMaxBytes) ? 1 : 0;
+    if (d.fused_slide || d.fused_linear) {
+        if ((rc = h->alloc(&d.part_res, copies * Nz * P * d.picard_blocks, "part_res"))) return rc;
+        if ((rc = h->alloc(&d.part_dev, copies * Nz * P * d.picard_blocks, "part_dev"))) return rc;
+    } else {
+        if ((rc = h->alloc(&d.part_rows, Nz * d.picard_blocks * 2 * P, "part_rows"))) return rc;
+    }
     if ((rc = h->alloc(&d.pre, copies * Nz, "pre"))) return rc;
     if (h->flags & PA_FLAG_TRACE)
         if ((rc = h->alloc(&d.trace, Nz * T, "trace"))) return rc;
