@@ -206,11 +206,17 @@ int setup_network(Dev& d, DevMem& mem, const pa_eps_model_t* em, const double* t
     // them, a workspace does not (what fits it stays as it was).
     const size_t groups = (size_t)Hd / 64;
     const size_t most = (size_t)mlp_fine_rows(Hd, d.ntok, d.mlp_grid);
-    size_t ep = (size_t)d.nsplit * ep_rows;
+    const size_t base = (size_t)d.nsplit * ep_rows;
     const size_t fine = most < ep_rows ? most : ep_rows;
+    size_t ep = base;
     if (!mem.ws && d.eps_mode && ep < fine * groups) ep = fine * groups;
+    if ((rc = mem.alloc(&d.Ep, ep * Dz, "Ep"))) {
+        if (ep == base) return rc;
+        ep = base;                                   // what fitted before still does
+        g_err.clear();
+        if ((rc = mem.alloc(&d.Ep, ep * Dz, "Ep"))) return rc;
+    }
     d.fine_rows = (int32_t)(ep / groups < fine ? ep / groups : fine);
-    if ((rc = mem.alloc(&d.Ep, ep * Dz, "Ep"))) return rc;
     PA_HIP(hipMemcpyAsync(w1r, em->w1, (size_t)Hd * 16 * 2, hipMemcpyHostToDevice, st));
     PA_HIP(hipMemcpyAsync(w2r, em->w2, (size_t)Hd * Hd * 2, hipMemcpyHostToDevice, st));
     PA_HIP(hipMemcpyAsync(w3r, em->w3, (size_t)Hd * 16 * 2, hipMemcpyHostToDevice, st));
