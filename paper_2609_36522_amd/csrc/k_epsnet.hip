@@ -475,7 +475,7 @@ __global__ __launch_bounds__(kWaves * 64) void k_eps_mlp(Dev d) {
     if (d.fused_slide) {
         // A launch queued after the one that finished the sample (that launch computed the last
         // slide and published done) has nothing to do: every block leaves at once.
-        if (d.ctrl->done) return;
+        if (ended_before(d, *d.ctrl)) return;
         static_assert(sizeof(SlideScratch) + 16 + kSlideSubDoubles * sizeof(double) <= sizeof(h1s),
                       "slide scratch must fit");
         SlideScratch& sc = *reinterpret_cast<SlideScratch*>(&h1s[0][0]);
@@ -494,7 +494,7 @@ __global__ __launch_bounds__(kWaves * 64) void k_eps_mlp(Dev d) {
             }
         } else {                             // first sweep after reset: the reset's window
             const Ctrl* c = d.ctrl;
-            const int m = c->done ? 0 : c->m;
+            const int m = c->m;
             for (int j = tid; j < m; j += NT) fmiss[j] = c->miss_idx[j];
             if (tid == 0) {
                 mpre[0] = 0;

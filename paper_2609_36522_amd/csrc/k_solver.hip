@@ -108,6 +108,7 @@ __global__ void k_reset(Dev d) {
         c->newest = 0;
         c->m = W;
         c->done = 0;
+        c->ended = 0;
         c->nonfinite = 0;
         c->c = 0;
         c->sweep = 0;
@@ -181,16 +182,17 @@ __global__ __launch_bounds__(COLS * ROWS, MINB) void k_picard(Dev d) {
     int s, e, newest;
     if constexpr (FUSED) {
         static_assert(LINEAR && ROWS * TPT <= kFusedLinearMaxWindow, "windows of this shape");
-        if (ctrl->done) return;
+        if (ended_before(d, *ctrl)) return;
         __shared__ SlideScratch sc;
         __shared__ double sub[2 * ROWS * TPT * kSlideSubs];
         Dev last = d;                       // the last sweep's partials
         const size_t stride = (size_t)d.N * d.P * d.picard_blocks;
-        last.part_res += (d.parity ^ 1) * stride;
-        last.part_dev += (d.parity ^ 1) * stride;
-        d.part_res += d.parity * stride;
-        d.part_dev += d.parity * stride;
-        const SlidePre pre = d.pre[(d.parity ^ 1) * d.N + n];
+        const int parity = d.sweep_id & 1;
+        last.part_res += (parity ^ 1) * stride;
+        last.part_dev += (parity ^ 1) * stride;
+        d.part_res += parity * stride;
+        d.part_dev += parity * stride;
+        const SlidePre pre = d.pre[(parity ^ 1) * d.N + n];
         slide_partials<kThr>(last, n, sub);
         for (int j = threadIdx.x; j < PA_MAX_WINDOW + TPT; j += kThr) sm[j] = 0;
         __syncthreads();
@@ -434,7 +436,7 @@ __global__ __launch_bounds__(COLS * ROWS, MINB) void k_picard(Dev d) {
     // Fused sweep: the state this sweep started from, for the slide of the next network kernel.
     if constexpr (FUSED) {
         // (Published by this block in slide_core, before several barriers; or by the reset.)
-        if (blockIdx.x == 0 && tid == 0) d.pre[d.parity * d.N + n] = slide_pre_of(*ctrl);
+        if (blockIdx.x == 0 && tid == 0) d.pre[(d.sweep_id & 1) * d.N + n] = slide_pre_of(*ctrl);
     } else if (d.fused_slide && blockIdx.x == 0 && tid == 0) {
         d.pre[n] = slide_pre_of(*ctrl);
     }
@@ -507,9 +509,10 @@ __global__ __launch_bounds__(kSlideThreads) void k_slide(Dev d) {
     __shared__ double sub[kSlideSubDoubles];
     if (FROM_PRE && d.fused_linear) {            // the last enqueued sweep's partials and snapshot
         const size_t stride = (size_t)d.N * d.P * d.picard_blocks;
-        d.part_res += d.parity * stride;
-        d.part_dev += d.parity * stride;
-        d.pre += d.parity * d.N;
+        const int parity = d.sweep_id & 1;
+        d.part_res += parity * stride;
+        d.part_dev += parity * stride;
+        d.pre += parity * d.N;
     }
     if (d.part_rows) slide_partials_rows<kSlideThreads>(d, n, sub);   // issued while the control block is read
     else slide_partials<kSlideThreads>(d, n, sub);

@@ -26,6 +26,7 @@ struct alignas(256) Ctrl {
     int32_t miss_idx[PA_MAX_WINDOW];  // ascending miss timesteps
     uint8_t slot_miss[PA_MAX_WINDOW]; // per window slot j: 1 if t = s + j is a miss
     uint8_t slot_rank[PA_MAX_WINDOW]; // per miss slot j: its position in miss_idx
+    int32_t ended;      // Dev::sweep_id of the launch that set done; 0 before
 };
 
 // The control-block fields the window slide reads, as they were before it (the fused sweep's
@@ -82,7 +83,7 @@ struct Dev {
     int32_t fused_slide;       // 1: the network kernel computes the slide (N = 1), no k_slide
     int32_t fused_linear;      // 1: the Picard kernel of a linear network computes the last
                                // sweep's slide itself, no k_slide
-    int32_t parity;            // fused_linear: of the sweep being enqueued
+    int32_t sweep_id;          // of the sweep enqueued last: never 0, odd and even in turn
     uint64_t* progress;        // [N] host-mapped words: sweeps << 32 | done << 31 | nonfinite << 30 | s
     uint64_t* counters;        // [N][4] host-mapped final counters (epoch << 40 | value) or null
     uint32_t epoch;            // sample epoch of the counter words (24 bits, set at reset)

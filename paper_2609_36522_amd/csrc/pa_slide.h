@@ -8,11 +8,23 @@
 // partial sums, never of the control block it writes: computing the same slide twice (a
 // finishing k_slide and then the next network kernel, or two network kernels without a Picard
 // kernel between them once the sample is done) writes the same values.
+//
+// In the fused sweeps block 0 publishes the slide while other blocks of the launch may not have
+// started or may have some of their waves past a load and some before it. These take nothing from
+// what it writes except whether the sample ended in an earlier launch (ended_before).
 #pragma once
 
 #include "pa_device.h"
 
 namespace pa {
+
+// For a kernel whose own launch may end the sample: did an earlier one? Ctrl::done cannot tell, since
+// a wave that reads it late sees this launch's: some waves of a block would leave and the others go
+// on without them. The id of the launch that ended the sample gives every wave the same answer.
+__device__ __forceinline__ bool ended_before(const Dev& d, const Ctrl& c) {
+    const int32_t id = c.ended;
+    return id != 0 && id != d.sweep_id;
+}
 
 // Sub-sums per reduced value, and the LDS they need (doubles): fixed, so the order of every
 // fp64 sum is the same in every kernel that computes the slide.
@@ -184,6 +196,7 @@ __device__ void slide_core(const Dev& d, int n, const SlidePre& pre, bool writer
             ctrl->s = s2;
             ctrl->e = min(s2 + d.P, d.T);
             ctrl->done = s2 >= d.T;
+            ctrl->ended = s2 >= d.T ? d.sweep_id : 0;
             ctrl->sweep = pre.sweep + 1;
             sc.nonfinite = (pre.nonfinite || anybad) ? 1 : 0;
         }

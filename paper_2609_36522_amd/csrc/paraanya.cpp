@@ -127,13 +127,13 @@ struct paraanya {
         // packets between kernels).
         ctrl_fresh = false;
         head_valid = false;
+        d.sweep_id = d.sweep_id == INT32_MAX ? 2 : d.sweep_id + 1;
         hipEvent_t e0, e1;
         int rc;
         if (model == PA_EPS_PATCH_MLP) {
             if ((rc = timed(0, &e0, &e1))) return rc;
             PA_HIP(pa::launch_eps_mlp(d, stream, e0, e1));
         }
-        if (d.fused_linear) d.parity ^= 1;
         if ((rc = timed(1, &e0, &e1))) return rc;
         PA_HIP(pa::launch_picard(d, stream, model == PA_EPS_LINEAR, e0, e1));
         if (d.fused_slide || d.fused_linear) {
