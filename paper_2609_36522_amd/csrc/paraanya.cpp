@@ -36,6 +36,8 @@ struct paraanya {
     pa::KernelTimer timer;            // kinds: 0 network, 1 Picard, 2 slide
     int64_t timed_latents = 0;        // network latents of the samples the timer covers
     bool slide_pending = false;       // fused sweep: the last sweep's slide is not computed yet
+    double revisit_thr = 0.05;        // for the sweeps enqueued from now on; d.revisit_thr is the one
+                                      // of the sweep whose slide the next launch computes
     bool head_valid = false;          // ctrl_host's counters are final (taken from the counter
                                       // words by paraanya_sample; work may still be queued)
     bool progress_quiet = false;      // nothing queued can still write a progress word
@@ -139,9 +141,11 @@ struct paraanya {
         if (d.fused_slide || d.fused_linear) {
             // The slide runs at the start of the next network (or Picard) kernel, or of a
             // finishing k_slide when the host needs the control block first.
+            d.revisit_thr = revisit_thr;
             slide_pending = true;
             return PA_OK;
         }
+        d.revisit_thr = revisit_thr;
         if ((rc = timed(2, &e0, &e1))) return rc;
         PA_HIP(pa::launch_slide(d, stream, e0, e1));
         return PA_OK;
@@ -204,7 +208,7 @@ int setup_handle(paraanya* h, const Request& q, const double* coef, const double
     Dev& d = h->d;
     d.N = q.N; d.T = q.T; d.P = q.P; d.D = q.D; d.C = q.C; d.Himg = q.Hi; d.Wimg = q.Wi;
     d.delta = q.delta; d.tol = q.tol;
-    d.revisit_thr = 0.05;
+    d.revisit_thr = h->revisit_thr;
     d.picard_blocks = pa::picard_blocks(q.D, q.P);
     h->model = q.em->kind;
     int dev_id = 0;
@@ -343,7 +347,7 @@ int paraanya_set_revisit_threshold(paraanya_t* h, double threshold) {
     pa::g_err.clear();
     if (!h) return fail(PA_ERR_INVALID_ARG, "NULL handle");
     if (!(threshold >= 0.0)) return fail(PA_ERR_INVALID_ARG, "threshold must be >= 0 (got %g)", threshold);
-    h->d.revisit_thr = threshold;
+    h->revisit_thr = threshold;
     return PA_OK;
 }
 

@@ -260,6 +260,33 @@ def test_revisit_threshold(gpu_lib):
         assert ei.value.code == B.PA_ERR_INVALID_ARG
 
 
+# One sample (fused sweeps) against the same sample among many (a slide launch per sweep).
+@pytest.mark.parametrize("wl,batch", [(W.TINY_LINEAR.with_(latent=(4, 32, 32), T=100, window=8), 9), (W.SMALL_MLP, 2)],
+                         ids=["linear", "mlp"])
+@pytest.mark.parametrize("sync", [False, True])
+def test_revisit_threshold_applies_to_later_sweeps(wl, batch, sync, gpu_lib):
+    """A threshold set between two sweeps counts for the sweeps enqueued after the call, whether
+    or not the host reads the counters in between, and counters once read stay."""
+    xb = torch.from_numpy(inputs.x_init_batch(wl.latent, batch)).cuda().reshape(batch, -1)
+    thr = (0.0, math.inf, 0.02, 0.0, 0.0, math.inf)
+
+    def run(count):
+        seen = []
+        with B.from_workload(wl, 0.0, batch=count) as s:
+            s.reset(xb[:count].contiguous())
+            for k in range(9):
+                s.set_revisit_threshold(thr[k % len(thr)])
+                s.sweep(sync=sync)
+                s.set_revisit_threshold(thr[(k + 1) % len(thr)])
+                if sync or k == 8:
+                    seen.append(s.stats(0))
+        return seen
+
+    one = run(1)
+    assert not one[-1]["done"] and one[-1]["revisits_below"] > 0
+    assert one == run(batch)
+
+
 def test_batch_argument_checks(gpu_lib):
     wl = W.TINY_LINEAR
     with B.from_workload(wl, batch=3, trace=True) as s:
