@@ -422,7 +422,7 @@ __global__ __launch_bounds__(COLS * ROWS, MINB) void k_picard(Dev d) {
     __syncthreads();
     const int nblk = gridDim.x;
     if (tid < W) {
-        if (FUSED || d.fused_slide) {
+        if (FUSED || !d.part_rows) {
             const size_t pbase = (size_t)n * d.P * nblk;
             d.part_res[pbase + tid * nblk + blockIdx.x] = rres[tid];
             d.part_dev[pbase + tid * nblk + blockIdx.x] = rdev[tid];

@@ -116,7 +116,8 @@ struct Dev {
     // Solver kernels only
     double* part_rows;                 // [N][picard_blocks][2P] part_res and part_dev with a Picard
                                        // block's partials in a row, for the sweeps that k_slide
-                                       // ends (part_res and part_dev are then null), or null
+                                       // of several samples ends (part_res and part_dev are then
+                                       // null), or null
 };
 
 // Kernel launchers (all asynchronous on `st`).

@@ -98,8 +98,11 @@ __device__ void slide_partials(const Dev& d, int n, double* sub) {
 // The same sub-sums from the row layout (part_rows): a Picard block's partials are contiguous, so
 // its stores fill whole lines of its own where slot by slot each was 8 bytes of a line shared with
 // 15 blocks on other XCDs (32 samples of 4x64x64, window 32, linear: Picard launch 43.7 -> 40.4
-// us, sample 397 -> 377), and a wave's load is one run. Only where k_slide reduces: in the network
-// kernel's prologue the slot layout is faster (one sample of 4x64x64, T = 100: 1024 against 1045 us).
+// us, sample 397 -> 377), and a wave's load is one run. Only for several samples whose slides run in
+// k_slide: in the network kernel's prologue the slot layout is faster (one sample of 4x64x64,
+// T = 100: 1024 against 1045 us), and so it is in k_slide where the stores are one sample's (linear,
+// one sample of 4x128x128, T = 100, window 16: 139 against 145 us; 4x96x96, T = 200, window 64: 183
+// against 187; k_slide 5.4 against 5.8 us a launch).
 template <int NT>
 __device__ void slide_partials_rows(const Dev& d, int n, double* sub) {
     const int nblk = d.picard_blocks, Q = 2 * d.P;

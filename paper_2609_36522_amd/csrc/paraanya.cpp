@@ -236,7 +236,8 @@ int setup_handle(paraanya* h, const Request& q, const double* coef, const double
     // kernel): one sample, patch-MLP, and a partial-sum volume that a block reduces quickly.
     d.fused_slide = (q.em->kind == PA_EPS_PATCH_MLP && q.N == 1 &&
                      part_bytes <= pa::kFusedSlideMaxBytes) ? 1 : 0;
-    if (d.fused_slide || d.fused_linear) {
+    // Several samples whose slides run in k_slide: their partials block by block (part_rows).
+    if (d.fused_slide || d.fused_linear || q.N == 1) {
         if ((rc = h->alloc(&d.part_res, copies * Nz * P * d.picard_blocks, "part_res"))) return rc;
         if ((rc = h->alloc(&d.part_dev, copies * Nz * P * d.picard_blocks, "part_dev"))) return rc;
     } else {

@@ -204,14 +204,20 @@ def test_stochastic_handle_needs_noise(gpu_lib):
 
 @pytest.mark.parametrize("wl,eta,N", [(W.TINY_LINEAR, 0.0, 4), (W.SMALL_MLP, 0.0, 4), (W.SD_MLP, 0.0, 4),
                                       (W.TINY_LINEAR, 1.0, 4), (W.SMALL_MLP, 1.0, 4),
-                                      (W.SD_MLP, 0.0, 8), (W.SMALL_MLP, 1.0, 8), (W.TINY_LINEAR, 0.0, 8)],
+                                      (W.SD_MLP, 0.0, 8), (W.SMALL_MLP, 1.0, 8), (W.TINY_LINEAR, 0.0, 8),
+                                      (W.TINY_LINEAR.with_(latent=(4, 32, 32), T=60, window=24), 0.0, 9),
+                                      (W.SMALL_MLP.with_(window=20), 1.0, 8),
+                                      (W.TINY_LINEAR.with_(latent=(4, 96, 96), T=40, window=8), 0.0, 2)],
                          ids=["linear", "mlp_small", "mlp_sd", "linear_ddpm", "mlp_small_ddpm",
-                              "mlp_sd_batch8", "mlp_small_ddpm_batch8", "linear_batch8"])
+                              "mlp_sd_batch8", "mlp_small_ddpm_batch8", "linear_batch8", "linear_batch9_capped",
+                              "mlp_small_ddpm_batch8_capped", "linear_slides_apart"])
 def test_batch_equals_independent_samples(wl, eta, N, gpu_lib):
     """A handle with N samples gives each sample exactly what a single-sample handle gives
-    it: the same final latent bit for bit, counters and sweep traces. Handles of eight or more
-    samples run the Picard kernel builds capped for occupancy (deterministic, stochastic and
-    linear-network builds)."""
+    it: the same final latent bit for bit, counters and sweep traces. Patch-MLP handles of eight or
+    more samples and windows of 17 to 32 run the Picard kernel builds capped for occupancy, and so
+    does linear_batch9_capped (fewer linear samples run one launch per sweep). linear_slides_apart:
+    a slide launch per sweep for one sample too, with its partial sums laid out by slot where those
+    of two are by block."""
     xb = inputs.x_init_batch(wl.latent, N).reshape(N, -1)
     Z = inputs.step_noise(N, wl.T, wl.D) if eta > 0 else None
     with B.from_workload(wl, batch=N, eta=eta, trace=True) as s:
