@@ -168,9 +168,9 @@ __device__ __forceinline__ double4 d4_zero() { return make_double4(0.0, 0.0, 0.0
 // MINB: minimum blocks per CU the compiler must fit (1, or 6 (5 with step noise or one
 // partial output) for the 256-thread shape of batched handles: at most 76 (96) registers). NOISE: the step adds the
 // pre-drawn noise term (stochastic sampler).
-// FUSED (linear network): every block first computes the slide of the last sweep itself, from its
-// partials and snapshot (the other parity's, so no block reads what this launch writes); block 0
-// of a sample publishes it.
+// FUSED (linear network, a slide outstanding): every block first computes the slide of the last
+// sweep itself, from its partials and snapshot (the other parity's, so no block reads what this
+// launch writes); block 0 of a sample publishes it.
 template <int COLS, int ROWS, int TPT, bool LINEAR, int NS, int MINB, bool NOISE, bool FUSED = false>
 __global__ __launch_bounds__(COLS * ROWS, MINB) void k_picard(Dev d) {
     constexpr int kThr = COLS * ROWS;
@@ -196,21 +196,14 @@ __global__ __launch_bounds__(COLS * ROWS, MINB) void k_picard(Dev d) {
         slide_partials<kThr>(last, n, sub);
         for (int j = threadIdx.x; j < PA_MAX_WINDOW + TPT; j += kThr) sm[j] = 0;
         __syncthreads();
-        if (pre.pending) {
-            slide_core<kThr>(last, n, pre, blockIdx.x == 0, sc, sub);
-            if (sc.done) return;
-            s = sc.s2;
-            e = min(s + d.P, d.T);
-            newest = sc.newest;
-            for (int j = threadIdx.x; j < sc.m; j += kThr) {
-                sm[sc.miss_idx[j] - s] = 1;
-                sr[sc.miss_idx[j] - s] = (uint8_t)j;
-            }
-        } else {                            // first sweep after reset: the reset's window, all misses
-            s = ctrl->s;
-            e = ctrl->e;
-            newest = ctrl->newest;
-            for (int j = threadIdx.x; j < e - s; j += kThr) sm[j] = 1;
+        slide_core<kThr>(last, n, pre, blockIdx.x == 0, sc, sub);
+        if (sc.done) return;
+        s = sc.s2;
+        e = min(s + d.P, d.T);
+        newest = sc.newest;
+        for (int j = threadIdx.x; j < sc.m; j += kThr) {
+            sm[sc.miss_idx[j] - s] = 1;
+            sr[sc.miss_idx[j] - s] = (uint8_t)j;
         }
     }
     // The network launch wrote the fresh outputs of the misses into Eh (whole outputs) rather
@@ -433,9 +426,9 @@ __global__ __launch_bounds__(COLS * ROWS, MINB) void k_picard(Dev d) {
         }
         if (blockIdx.x == 0 && (FUSED ? sm[tid] : ctrl->slot_miss[tid])) d.valid[(size_t)n * d.T + s + tid] = 1;   // Eq. (7) entry
     }
-    // Fused sweep: the state this sweep started from, for the slide of the next network kernel.
+    // Fused sweep: the state this sweep started from, for the slide of the next sweep's kernel.
     if constexpr (FUSED) {
-        // (Published by this block in slide_core, before several barriers; or by the reset.)
+        // (Published by this block in slide_core, before several barriers.)
         if (blockIdx.x == 0 && tid == 0) d.pre[(d.sweep_id & 1) * d.N + n] = slide_pre_of(*ctrl);
     } else if (d.fused_slide && blockIdx.x == 0 && tid == 0) {
         d.pre[n] = slide_pre_of(*ctrl);
@@ -443,7 +436,7 @@ __global__ __launch_bounds__(COLS * ROWS, MINB) void k_picard(Dev d) {
 }
 
 template <bool LINEAR, int NS, bool NOISE>
-static hipError_t launch_picard_t(const Dev& d, hipStream_t st, hipEvent_t e0, hipEvent_t e1) {
+static hipError_t launch_picard_t(Dev d, hipStream_t st, hipEvent_t e0, hipEvent_t e1, int pending) {
     const PicardShape sh = picard_shape(d.P);
     const dim3 grid(d.picard_blocks, d.N), block(sh.cols * sh.rows);
     if (d.picard_blocks != picard_blocks(d.D, d.P)) return hipErrorInvalidValue;
@@ -453,7 +446,7 @@ static hipError_t launch_picard_t(const Dev& d, hipStream_t st, hipEvent_t e0, h
     // there). With four partial outputs the register cap would spill.
     const bool occ = d.N >= 8;
     if constexpr (LINEAR) {
-        if (d.fused_linear) {
+        if (d.fused_linear && pending) {
             switch (sh.rows * 4 + sh.tpt) {
                 case 16 * 4 + 1: hipExtLaunchKernelGGL((k_picard<16, 16, 1, LINEAR, NS, 1, NOISE, true>), grid, block, 0, st, e0, e1, 0, d); break;
                 case 16 * 4 + 2: hipExtLaunchKernelGGL((k_picard<16, 16, 2, LINEAR, NS, 1, NOISE, true>), grid, block, 0, st, e0, e1, 0, d); break;
@@ -461,6 +454,15 @@ static hipError_t launch_picard_t(const Dev& d, hipStream_t st, hipEvent_t e0, h
                 default: return hipErrorInvalidValue;
             }
             return hipGetLastError();
+        }
+        if (d.fused_linear) {
+            // No slide outstanding (after a reset, or a finishing k_slide): the window is in the
+            // control block. Partials and snapshot of this sweep's parity for the next one.
+            const size_t parity = d.sweep_id & 1;
+            d.part_res += parity * d.N * d.P * d.picard_blocks;
+            d.part_dev += parity * d.N * d.P * d.picard_blocks;
+            d.pre += parity * d.N;
+            d.fused_slide = 1;
         }
     }
     switch (sh.rows * 4 + sh.tpt) {
@@ -484,18 +486,19 @@ static hipError_t launch_picard_t(const Dev& d, hipStream_t st, hipEvent_t e0, h
 }
 
 template <bool NOISE>
-static hipError_t launch_picard_n(const Dev& d, hipStream_t st, int linear, hipEvent_t e0, hipEvent_t e1) {
-    if (linear) return launch_picard_t<true, 1, NOISE>(d, st, e0, e1);
+static hipError_t launch_picard_n(const Dev& d, hipStream_t st, int linear, hipEvent_t e0, hipEvent_t e1, int pending) {
+    if (linear) return launch_picard_t<true, 1, NOISE>(d, st, e0, e1, pending);
     switch (d.nsplit) {
-        case 1: return launch_picard_t<false, 1, NOISE>(d, st, e0, e1);
-        case 2: return launch_picard_t<false, 2, NOISE>(d, st, e0, e1);
-        case 4: return launch_picard_t<false, 4, NOISE>(d, st, e0, e1);
+        case 1: return launch_picard_t<false, 1, NOISE>(d, st, e0, e1, pending);
+        case 2: return launch_picard_t<false, 2, NOISE>(d, st, e0, e1, pending);
+        case 4: return launch_picard_t<false, 4, NOISE>(d, st, e0, e1, pending);
         default: return hipErrorInvalidValue;
     }
 }
 
-hipError_t launch_picard(const Dev& d, hipStream_t st, int linear, hipEvent_t e0, hipEvent_t e1) {
-    return d.noise ? launch_picard_n<true>(d, st, linear, e0, e1) : launch_picard_n<false>(d, st, linear, e0, e1);
+hipError_t launch_picard(const Dev& d, hipStream_t st, int linear, hipEvent_t e0, hipEvent_t e1, int pending) {
+    return d.noise ? launch_picard_n<true>(d, st, linear, e0, e1, pending)
+                   : launch_picard_n<false>(d, st, linear, e0, e1, pending);
 }
 
 // ---------------------------------------------------------------------------- slide

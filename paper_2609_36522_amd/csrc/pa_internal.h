@@ -82,7 +82,7 @@ struct Dev {
     SlidePre* pre;             // [N] pre-slide snapshots (fused sweep; [2][N] with fused_linear)
     int32_t fused_slide;       // 1: the network kernel computes the slide (N = 1), no k_slide
     int32_t fused_linear;      // 1: the Picard kernel of a linear network computes the last
-                               // sweep's slide itself, no k_slide
+                               // sweep's slide itself if it is outstanding, no k_slide
     int32_t sweep_id;          // of the sweep enqueued last: never 0, odd and even in turn
     uint64_t* progress;        // [N] host-mapped words: sweeps << 32 | done << 31 | nonfinite << 30 | s
     uint64_t* counters;        // [N][4] host-mapped final counters (epoch << 40 | value) or null
@@ -136,7 +136,8 @@ constexpr size_t kFusedSlideMaxBytes = 256 * 1024;
 constexpr size_t kFusedLinearMaxBytes = 32 * 1024;
 constexpr int kFusedLinearMaxWindow = 64;
 constexpr long long kFusedLinearMaxBlocks = 512;
-hipError_t launch_picard(const Dev& d, hipStream_t st, int linear, hipEvent_t start, hipEvent_t stop);
+// pending: the last sweep's slide is outstanding (fused_linear: the kernel computes it).
+hipError_t launch_picard(const Dev& d, hipStream_t st, int linear, hipEvent_t start, hipEvent_t stop, int pending);
 // single: the launch evaluates at most one latent.
 hipError_t launch_eps_mlp(const Dev& d, hipStream_t st, hipEvent_t start, hipEvent_t stop, int single = 0);
 // List entries up to which a launch may take items that leave partial outputs per 64 units.

@@ -56,7 +56,8 @@ struct paraanya {
         if (ctrl_fresh) return PA_OK;
         if (slide_pending) {
             // Fused sweep: bring the control block up to date (the next network kernel computes
-            // the same slide again and writes the same values).
+            // the same slide again and writes the same values; the next Picard kernel of a linear
+            // network takes it from the control block).
             PA_HIP(pa::launch_slide_pending(d, stream));
             slide_pending = false;
         }
@@ -137,7 +138,7 @@ struct paraanya {
             PA_HIP(pa::launch_eps_mlp(d, stream, e0, e1));
         }
         if ((rc = timed(1, &e0, &e1))) return rc;
-        PA_HIP(pa::launch_picard(d, stream, model == PA_EPS_LINEAR, e0, e1));
+        PA_HIP(pa::launch_picard(d, stream, model == PA_EPS_LINEAR, e0, e1, slide_pending));
         if (d.fused_slide || d.fused_linear) {
             // The slide runs at the start of the next network (or Picard) kernel, or of a
             // finishing k_slide when the host needs the control block first.

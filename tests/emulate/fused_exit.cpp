@@ -109,7 +109,7 @@ void linear(int T, int P) {
     for (int past = 0; past < 3; past += done(d)) {
         ++d.sweep_id;
         in_every_order("linear sweep", a, launches++, [&] { return done(d); },
-                       [&] { launch_picard(d, nullptr, 1, nullptr, nullptr); });
+                       [&] { launch_picard(d, nullptr, 1, nullptr, nullptr, launches > 1); });
         if (launches > 4 * T) abort();
     }
     // a slide launch per sweep
@@ -117,7 +117,7 @@ void linear(int T, int P) {
     launch_reset(e, nullptr);
     int sweeps = 0;
     for (; !e.ctrl->done; ++sweeps) {
-        launch_picard(e, nullptr, 1, nullptr, nullptr);
+        launch_picard(e, nullptr, 1, nullptr, nullptr, 0);
         launch_slide(e, nullptr, nullptr, nullptr);
     }
     const size_t row = d.D * sizeof(float);
@@ -148,14 +148,14 @@ void network(int hidden) {
     d.fused_slide = 1;
     launch_reset(d, nullptr);
     ++d.sweep_id;
-    launch_picard(d, nullptr, 0, nullptr, nullptr);     // outputs of zero, in Ep
+    launch_picard(d, nullptr, 0, nullptr, nullptr, 0);     // outputs of zero, in Ep
     int launches = 0;
     for (int k = 0; k < 3; ++k) {
         ++d.sweep_id;
         in_every_order("network launch", a, launches++, [&] { return done(d); },
                        [&] { launch_eps_mlp(d, nullptr, nullptr, nullptr, 0); });
         expect(done(d) && d.ctrl->done, "network launch: end of the sample", launches, -1);
-        launch_picard(d, nullptr, 0, nullptr, nullptr);
+        launch_picard(d, nullptr, 0, nullptr, nullptr, 0);
     }
     printf("network H %d: %d launches ok\n", hidden, launches);
 }

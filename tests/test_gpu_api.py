@@ -376,7 +376,7 @@ def test_few_misses_equal_split_outputs(latent, hidden, P, batch, gpu_lib):
 def test_linear_one_launch_sweep_equals_two(latent, T, P, N, eta, gpu_lib):
     """A few linear samples run with one launch per sweep (the Picard kernel computes the last
     sweep's slide), many with two: the same states, cache, counters and traces, bit for bit,
-    sampled twice in a row and swept one by one."""
+    sampled twice in a row and swept one by one, read after every sweep or after every third."""
     c = inputs.linear_coefficients(T)
     xb = torch.from_numpy(inputs.x_init_batch(latent, N)).cuda().reshape(N, -1)
     z = torch.from_numpy(inputs.step_noise(N, T, xb.shape[1])).cuda()
@@ -388,15 +388,16 @@ def test_linear_one_launch_sweep_equals_two(latent, T, P, N, eta, gpu_lib):
             x = xb[first:first + count].contiguous()
             if stepwise:
                 s.reset(x)
-                while not s.sweep(sync=True):
-                    pass
+                k = 1
+                while not s.sweep(sync=k % stepwise == 0):
+                    k += 1
             else:
                 s.sample(x)
                 s.sample(x)
             return [(s.stats(n), s.traces(n), s.read_state(0, None, n)) for n in range(count)]
 
-    big = run(0, N, False)
-    for n, stepwise in ((0, False), (N - 1, False), (1, True)):
+    big = run(0, N, 0)
+    for n, stepwise in ((0, 0), (N - 1, 0), (1, 1), (2, 3)):
         (st0, tr0, S0), (st1, tr1, S1) = big[n], run(n, 1, stepwise)[0]
         assert st0 == st1 and len(tr0) == len(tr1)
         for a, b in zip(tr0, tr1):
