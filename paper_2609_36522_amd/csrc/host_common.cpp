@@ -202,8 +202,9 @@ int setup_network(Dev& d, DevMem& mem, const pa_eps_model_t* em, const double* t
     if ((rc = mem.alloc(&d.temb, (size_t)T * Hd, "temb"))) return rc;
     d.nsplit = mlp_splits(Hd);
     // Ep holds the halves' partial outputs of every row. Partial outputs per 64 units take the
-    // same buffer for as many list entries as fit; a handle's own buffer grows by up to 8 MB for
-    // them, a workspace does not (what fits it stays as it was).
+    // same buffer for as many list entries as fit; a handle's own buffer grows by up to 2 MB (at
+    // 256 blocks) for the entries that can take them, a workspace does not (what fits it stays as
+    // it was).
     const size_t groups = (size_t)Hd / 64;
     const size_t most = (size_t)mlp_fine_rows(Hd, d.ntok, d.mlp_grid);
     const size_t base = (size_t)d.nsplit * ep_rows;

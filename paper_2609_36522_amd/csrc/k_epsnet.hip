@@ -983,10 +983,9 @@ int mlp_splits(int hidden) { return hidden / kNH; }
 
 int mlp_grid_size(int device_cus) { return device_cus > 0 ? device_cus : 256; }
 
-int mlp_fine_rows(int hidden, int ntok, int grid) {
-    const long long rows = 2ll * grid * 64 * 256 / ((long long)ntok * hidden);
-    return rows < 1 ? 1 : (int)rows;
-}
+// The most list entries whose items of 32 tokens x 256 units fit the blocks in one round, as
+// fine_choice has it (0: one entry does not).
+int mlp_fine_rows(int hidden, int ntok, int grid) { return grid / ((ntok / 32) * (hidden / 256)); }
 
 hipError_t launch_eps_mlp(const Dev& d, hipStream_t st, hipEvent_t start, hipEvent_t stop, int single) {
     const dim3 grid(d.mlp_grid), block(kWaves * 64);

@@ -31,3 +31,7 @@ def emulated(tmp_path_factory):
 
 def test_blocks_of_a_fused_sweep_leave_whole(emulated):
     assert "fused exit ok" in emulated("fused_exit", ["k_solver.hip", "k_epsnet.hip"])
+
+
+def test_rows_of_fine_partial_outputs(emulated):
+    assert "fine rows ok" in emulated("fine_rows", [])
