@@ -430,9 +430,8 @@ __device__ __forceinline__ int fine_choice(int M, int ntok, int fine_rows, int G
     return sl * (H / 128) > G ? FINE_32x256 : FINE_32x128;
 }
 
-// TOK: tokens per work item, 128; or 64 for launches of a single latent of a wide network (H = 2048)
-// whose items of 32 tokens x 512 units do not fit the blocks in one round: its h1 GELUs meet the W2
-// stream, where a fine item of 64 tokens takes them in turn (2304 tokens: 39 against 43 us).
+// TOK: tokens per work item, 128; or 64 for some launches of a single latent (launch_eps_mlp): its h1
+// GELUs meet the W2 stream, where a fine item of 64 tokens takes them in turn.
 template <int H, int TOK>
 __global__ __launch_bounds__(kWaves * 64) void k_eps_mlp(Dev d) {
     constexpr int NT = kWaves * 64;
@@ -989,10 +988,19 @@ int mlp_fine_rows(int hidden, int ntok, int grid) { return grid / ((ntok / 32) *
 
 hipError_t launch_eps_mlp(const Dev& d, hipStream_t st, hipEvent_t start, hipEvent_t stop, int single) {
     const dim3 grid(d.mlp_grid), block(kWaves * 64);
-    const bool tok64 = single && d.hidden == 2048 && d.ntok / 32 * (d.hidden / 512) > d.mlp_grid;
+    // A single latent in 64-token items where those fit the blocks in one round and the fine items of
+    // 32 tokens x 512 units do not. Without -> with them, Parareal samples of 15 such launches and one
+    // of 8 latents: H = 1024, 4608 tokens 600 -> 566 us, 6400 664 -> 632, 8192 719 -> 692; one launch
+    // at H = 2048, 2304 tokens 43 -> 39 us. Beyond one round the 128-token kernel with its cut last
+    // round is faster (H = 1024, 9216 tokens 870 against 1001 us; H = 2048, 5120 1319 against 1513,
+    // 6400 1505 against 1630), and at H = 512 it is nowhere slower (9216 tokens 448 us either way,
+    // 12544 485 against 491).
+    const int it32 = d.ntok / 32 * (d.hidden / 512);
+    const bool tok64 = single && d.hidden >= 1024 && it32 > d.mlp_grid && it32 <= 2 * d.mlp_grid;
     switch (d.hidden + (tok64 ? 1 : 0)) {
         case 512: hipExtLaunchKernelGGL((k_eps_mlp<512, 128>), grid, block, 0, st, start, stop, 0, d); break;
         case 1024: hipExtLaunchKernelGGL((k_eps_mlp<1024, 128>), grid, block, 0, st, start, stop, 0, d); break;
+        case 1024 + 1: hipExtLaunchKernelGGL((k_eps_mlp<1024, 64>), grid, block, 0, st, start, stop, 0, d); break;
         case 2048: hipExtLaunchKernelGGL((k_eps_mlp<2048, 128>), grid, block, 0, st, start, stop, 0, d); break;
         case 2048 + 1: hipExtLaunchKernelGGL((k_eps_mlp<2048, 64>), grid, block, 0, st, start, stop, 0, d); break;
         default:

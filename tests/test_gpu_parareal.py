@@ -213,3 +213,23 @@ def test_parareal_nonfinite_input_never_hits(Bk, gpu_lib):
         st = s.stats()
         assert st["hits"] == 0 and st["nfe"] == st["requests"]
         assert all(not s.trace(i)[0]["hit"] for i in range(st["requests"]))
+
+
+# On 256 CUs: the fewest and the most tokens that coarse requests evaluate in 64-token items, and
+# the nearest counts that they do not (a multiple of 128 tokens each).
+@pytest.mark.parametrize("hidden,latent", [(1024, (4, 128, 128)), (1024, (4, 132, 128)), (1024, (4, 128, 256)),
+                                           (1024, (4, 260, 128)), (2048, (4, 64, 128)), (2048, (4, 68, 128)),
+                                           (2048, (4, 128, 128)), (2048, (4, 132, 128)), (512, (4, 192, 192))])
+def test_coarse_request_equals_sampler_output(hidden, latent, gpu_lib):
+    """The items a launch of a single latent takes do not change its bits: the first coarse
+    request's output is the sampler's first, taken in 128-token items with split outputs."""
+    x = torch.from_numpy(inputs.x_init(latent).reshape(-1)).cuda()
+    kw = {"weights": inputs.mlp_weights(hidden), "hidden": hidden}
+    with B.Parareal(latent, 2, 2, 0.0, INF, "patch_mlp", trace=True, **kw) as s:
+        s.sample(x)
+        rec, eps = s.trace(0, with_eps=True)
+    assert rec["t"] == 0 and not rec["hit"]
+    with B.Sampler(latent, 2, 1, 0.0, INF, "patch_mlp", split_outputs=True, **kw) as s:
+        s.sample(x)
+        _, _, Eh, _ = s.read_state(0, 1)
+    assert np.array_equal(eps, Eh[0])
