@@ -121,12 +121,12 @@ __device__ __forceinline__ int korder(int odd, int i) {
 
 // Fine items, for launches whose 128-token items would leave most CUs without work: item =
 // (list entry, 32 TS tokens, UF output units). The block computes h1 of all H units of its tokens
-// into LDS once (KP = 2: half of K at a time), then GEMM2 from there; each wave owns 32 (UF < 512) or 64 output units, and its
-// W2^T fragments are in flight from before the gather. Every accumulation runs in the order of
-// the 128-token items (K-chunks, the 64 units of a GEMM3 chain, the waves of a half), so the
-// outputs are the same bits. UF = 512 covers a half and writes its split partial output; a
-// smaller UF writes one partial output per 64 units (a wave's share of a half) to
-// Ep[group][list entry], and the consumer adds them in the order the half's reduction takes.
+// into LDS once (KP = 2: half of K at a time), then GEMM2 from there; each wave owns 32 (UF < 512)
+// or 64 output units, and its W2^T fragments are in flight from before the gather. Every
+// accumulation runs in the order of the 128-token items (K-chunks, the 64 units of a GEMM3 chain,
+// the waves of a half), so the outputs are the same bits. UF = 512 covers a half and writes its
+// split partial output; a smaller UF writes one partial output per 64 units (a wave's share of a
+// half) to Ep[group][list entry], and the consumer adds them in the order the half's reduction takes.
 // Bound by one CU's stream of W2^T from L2 (UF x H x 2 bytes at ~46 B/clk: 2.2 us at UF = 128,
 // H = 1024) after its h1 GELUs (2.4 us per 32 tokens at H = 1024), hence few units and few tokens
 // per item while CUs are free. Launch time with 128-token items -> with these (1024 tokens,
@@ -146,13 +146,11 @@ __device__ __forceinline__ void fine_items(const Dev& d, __bf16* h1, __bf16* xs,
     static_assert(!WHOLE || (UF == kNH && KP == 1), "h1 of all units serves every half");
     constexpr int UBW = UF == 512 ? 2 : 1;           // 32-unit blocks per wave
     constexpr int UB = UF / 32;                      // 32-unit blocks per item
-    constexpr bool kSplitTok = UB == 4 && TS > 1;    // two wave groups, each half of the token slices
-    constexpr int SL = kSplitTok ? TS / 2 : TS;      // token slices per wave
     // k-steps of W2^T fragments in flight: half of K at UBW = 1 (one wave's 32 KB at H = 1024; 16
     // steps leave the stream waiting for round trips, 50 serial steps 882 against 866 us).
     constexpr int DEPTH = UBW == 2 ? 8 : (H == 512 ? 16 : 32);
     constexpr int KCP = KCH / KP;                    // K-chunks (and h1 unit blocks per wave) per pass
-    static_assert(UF == 128 || UF == 256 || UF == 512, "whole GEMM3 chains (64 units)");
+    static_assert(UF == 512 || (TS == 1 && (UF == 128 || UF == 256)), "whole GEMM3 chains (64 units)");
     static_assert(KS / KP % DEPTH == 0, "whole fragment groups");
     const int tid = threadIdx.x, lane = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -161,8 +159,7 @@ __device__ __forceinline__ void fine_items(const Dev& d, __bf16* h1, __bf16* xs,
         const_cast<__bf16*>(d.w2f), (short)0, H * H * 2, 0x00020000);
     const f32x16 zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f,
                            0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    const bool active = UB >= 8 || kSplitTok || w < UB;
-    const int sl0 = kSplitTok ? (w >> 2) * SL : 0;   // this wave's first token slice
+    const bool active = UB >= 8 || w < UB;
     for (int item = blockIdx.x; item < items; item += gridDim.x) {
         const FineItem it = map(item);
         const int gm = it.gm, tb = it.tb;
@@ -219,8 +216,8 @@ __device__ __forceinline__ void fine_items(const Dev& d, __bf16* h1, __bf16* xs,
             if (tid + k * NT < H / 4) reinterpret_cast<float4*>(es)[tid + k * NT] = ev[k];
         __syncthreads();
 
-        f32x16 acc[UBW][SL];
-        const __bf16* hb = h1 + (sl0 * 32 + l32) * HR + g * 8;
+        f32x16 acc[UBW][TS];
+        const __bf16* hb = h1 + l32 * HR + g * 8;
         // DEPTH k-steps from k-step i0 of the half's order; reloads the stages if more follow.
         constexpr int KSP = KS / KP;                 // k-steps per pass
         auto steps = [&](int hf, int i0, auto more_c) {
@@ -229,12 +226,12 @@ __device__ __forceinline__ void fine_items(const Dev& d, __bf16* h1, __bf16* xs,
             for (int j = 0; j < DEPTH; ++j) {
                 if (j % 16 == 0)
                     p0 = KP == 1 ? korder<KCH>((ns0 + hf) & 1, (i0 + j) / 16) * kKC + i0 % 16 * 16 : (i0 + j) % KSP * 16;
-                bf16x8 B[SL];
+                bf16x8 B[TS];
 #pragma unroll
-                for (int sl = 0; sl < SL; ++sl)
+                for (int sl = 0; sl < TS; ++sl)
                     B[sl] = *reinterpret_cast<const bf16x8*>(hb + sl * 32 * HR + p0 + j % 16 * 16);
 #pragma unroll
-                for (int sl = 0; sl < SL; ++sl)
+                for (int sl = 0; sl < TS; ++sl)
 #pragma unroll
                     for (int u = 0; u < UBW; ++u) acc[u][sl] = mfma32(A[j][u], B[sl], acc[u][sl]);
                 if constexpr (decltype(more_c)::value) load_a(hf, i0 + DEPTH + j, j);
@@ -244,7 +241,7 @@ __device__ __forceinline__ void fine_items(const Dev& d, __bf16* h1, __bf16* xs,
 #pragma unroll
             for (int u = 0; u < UBW; ++u)
 #pragma unroll
-                for (int sl = 0; sl < SL; ++sl) acc[u][sl] = zero16;
+                for (int sl = 0; sl < TS; ++sl) acc[u][sl] = zero16;
         };
         zero_acc();
 #pragma unroll
@@ -288,14 +285,14 @@ __device__ __forceinline__ void fine_items(const Dev& d, __bf16* h1, __bf16* xs,
         }
 
         // ---- GEMM3: chains of 64 units (two unit blocks) per token slice
-        f32x16 acc3[SL];
+        f32x16 acc3[TS];
         auto gemm3 = [&](int ub0, int u) {
 #pragma unroll
             for (int jj = 0; jj < 2; ++jj) {
                 const bf16x8 a3 = *reinterpret_cast<const bf16x8*>(
                     d.w3p + (((size_t)(ub0 + u) * 2 + jj) * 64 + lane) * 8);
 #pragma unroll
-                for (int sl = 0; sl < SL; ++sl) {
+                for (int sl = 0; sl < TS; ++sl) {
                     bf16x8 b3;
 #pragma unroll
                     for (int i = 0; i < 8; ++i) b3[i] = (__bf16)gelu2_erf(acc[u][sl][jj * 8 + i]);
@@ -304,13 +301,13 @@ __device__ __forceinline__ void fine_items(const Dev& d, __bf16* h1, __bf16* xs,
             }
         };
 #pragma unroll
-        for (int sl = 0; sl < SL; ++sl) acc3[sl] = zero16;
+        for (int sl = 0; sl < TS; ++sl) acc3[sl] = zero16;
         const int half_w = d.Wimg >> 1;
         float* red = reinterpret_cast<float*>(h1);
         if constexpr (UBW == 2) {
             // WHOLE: the first half's sums wait in registers (8 per slice) while the second takes
             // h1, which the reduction overwrites.
-            float keep[SL][8];
+            float keep[TS][8];
             if constexpr (NH == 2) {
 #pragma unroll
                 for (int j = 0; j < DEPTH; ++j) load_a(1, j, j);
@@ -319,7 +316,7 @@ __device__ __forceinline__ void fine_items(const Dev& d, __bf16* h1, __bf16* xs,
             gemm3(ub00, 1);
             if constexpr (NH == 2) {
 #pragma unroll
-                for (int sl = 0; sl < SL; ++sl) {
+                for (int sl = 0; sl < TS; ++sl) {
 #pragma unroll
                     for (int r = 0; r < 8; ++r) keep[sl][r] = acc3[sl][r];
                     acc3[sl] = zero16;
@@ -336,7 +333,7 @@ __device__ __forceinline__ void fine_items(const Dev& d, __bf16* h1, __bf16* xs,
             for (int hf = 0; hf < NH; ++hf) {
                 __syncthreads();                         // h1 operands, or the last half's sums, are read
 #pragma unroll
-                for (int sl = 0; sl < SL; ++sl) {
+                for (int sl = 0; sl < TS; ++sl) {
                     float* dst = red + ((size_t)w * kTok + sl * 32 + l32) * kFeat + g * 4;
                     const bool kept = NH == 2 && hf == 0;
                     float v[8];
@@ -370,12 +367,12 @@ __device__ __forceinline__ void fine_items(const Dev& d, __bf16* h1, __bf16* xs,
             // The wave of the chain's first unit block hands its sums to the wave of the second
             // (rows 0..15 of the tile: accumulator registers 0..7).
             const bool first = (ub00 & 1) == 0;
-            float* pass = red + ((size_t)(w & ~1) * SL * 64 + lane) * 8;
+            float* pass = red + ((size_t)(w & ~1) * TS * 64 + lane) * 8;
             if (active && first) gemm3(ub00, 0);
             __syncthreads();                         // every wave has read its h1 operands
             if (active && first) {
 #pragma unroll
-                for (int sl = 0; sl < SL; ++sl) {
+                for (int sl = 0; sl < TS; ++sl) {
                     float4* p = reinterpret_cast<float4*>(pass + (size_t)sl * 64 * 8);
                     p[0] = make_float4(acc3[sl][0], acc3[sl][1], acc3[sl][2], acc3[sl][3]);
                     p[1] = make_float4(acc3[sl][4], acc3[sl][5], acc3[sl][6], acc3[sl][7]);
@@ -384,7 +381,7 @@ __device__ __forceinline__ void fine_items(const Dev& d, __bf16* h1, __bf16* xs,
             __syncthreads();
             if (active && !first) {
 #pragma unroll
-                for (int sl = 0; sl < SL; ++sl) {
+                for (int sl = 0; sl < TS; ++sl) {
                     const float4* p = reinterpret_cast<const float4*>(pass + (size_t)sl * 64 * 8);
                     const float4 a = p[0], b = p[1];
                     acc3[sl][0] = a.x;
@@ -400,8 +397,8 @@ __device__ __forceinline__ void fine_items(const Dev& d, __bf16* h1, __bf16* xs,
                 // Lane (g, token): features 4g..4g+3 (channel g) and 8+4g.. (channel 2+g).
                 float* ep = d.Ep + ((size_t)(ub00 >> 1) * d.fine_rows + gm) * d.D;
 #pragma unroll
-                for (int sl = 0; sl < SL; ++sl) {
-                    const int tok = tb * kTok + (sl0 + sl) * 32 + l32, hp = tok / half_w, wp = tok - hp * half_w;
+                for (int sl = 0; sl < TS; ++sl) {
+                    const int tok = tb * kTok + sl * 32 + l32, hp = tok / half_w, wp = tok - hp * half_w;
 #pragma unroll
                     for (int q = 0; q < 2; ++q) {
                         float* o = ep + ((size_t)(2 * q + g) * d.Himg + 2 * hp) * d.Wimg + 2 * wp;
@@ -585,7 +582,6 @@ __global__ __launch_bounds__(kWaves * 64) void k_eps_mlp(Dev d) {
         const_cast<__bf16*>(d.w2f), (short)0, H * H * 2, 0x00020000);
     const f32x16 zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f,
                            0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    // Whole outputs: each thread's sum of the halves so far, in LDS to keep four registers free.
     // Whole outputs: each thread's sum of the halves so far. In LDS where there are two: four
     // registers less across GEMM2, without which some were spilled, and a kernel with scratch
     // memory takes longer to start as well (8 x 1024 tokens, H = 1024: 6755 -> 6707 us a sample).

@@ -99,16 +99,6 @@ __device__ __forceinline__ double block_sum_step(double v, double* sh) {
     return s;
 }
 
-__device__ __forceinline__ double abs_dev(float4 a, float4 b) {
-    return (fabs((double)a.x - (double)b.x) + fabs((double)a.y - (double)b.y)) +
-           (fabs((double)a.z - (double)b.z) + fabs((double)a.w - (double)b.w));
-}
-
-__device__ __forceinline__ double sq_dev(float4 a, float4 b) {
-    const double dx = (double)a.x - b.x, dy = (double)a.y - b.y, dz = (double)a.z - b.z, dw = (double)a.w - b.w;
-    return (dx * dx + dy * dy) + (dz * dz + dw * dw);
-}
-
 __global__ __launch_bounds__(kTestThreads) void k_pr_test(Dev d, PrArgs a) {
     const int n = blockIdx.x;
     Ctrl* c = d.ctrl + n;

@@ -6,13 +6,13 @@
 // is done makes its blocks exit at once.
 //   k_picard : Eq. (6) assembly (cached output for hits, fresh for misses: in the cache
 //              already when the network launch wrote whole outputs, else the fixed-order sum
-//              of its split partials), Eq. (7) cache update, DDIM drift at the current latents, the Eq. (1) prefix sum over the
-//              window anchored at its start (blocked scan: register scan per thread, chunk
-//              carries through LDS). Per block it writes partial sums of the Eq. (2)
-//              residuals and, for the states it just updated, of the Eq. (4) deviation from
-//              the cache entry they will be tested against in the next sweep (every drift
-//              point of the window holds a cache entry after the sweep), so the next sweep
-//              needs no separate pass over the window.
+//              of its partials), Eq. (7) cache update, DDIM drift at the current latents, the
+//              Eq. (1) prefix sum over the window anchored at its start (blocked scan: register
+//              scan per thread, chunk carries through LDS). Per block it writes partial sums of
+//              the Eq. (2) residuals and, for the states it just updated, of the Eq. (4)
+//              deviation from the cache entry they will be tested against in the next sweep
+//              (every drift point of the window holds a cache entry after the sweep), so the
+//              next sweep needs no separate pass over the window.
 //   k_slide  : residuals from the partials, leading converged count, window slide, done;
 //              then, for the next window, Eq. (5) hit test (first entries are misses) and
 //              ballot + LDS-offset compaction of the misses into an ascending list.
@@ -65,17 +65,6 @@ __device__ __forceinline__ double4 drift(double alpha, float4 x, double b, float
 __device__ __forceinline__ double4 add_noise(double4 d, double sigma, float4 z) {
     return make_double4(fma(sigma, (double)z.x, d.x), fma(sigma, (double)z.y, d.y),
                         fma(sigma, (double)z.z, d.z), fma(sigma, (double)z.w, d.w));
-}
-
-__device__ __forceinline__ double abs_dev(float4 a, float4 b) {
-    return (fabs((double)a.x - (double)b.x) + fabs((double)a.y - (double)b.y)) +
-           (fabs((double)a.z - (double)b.z) + fabs((double)a.w - (double)b.w));
-}
-
-__device__ __forceinline__ double sq_dev(float4 a, float4 b) {
-    const double dx = (double)a.x - (double)b.x, dy = (double)a.y - (double)b.y;
-    const double dz = (double)a.z - (double)b.z, dw = (double)a.w - (double)b.w;
-    return (dx * dx + dy * dy) + (dz * dz + dw * dw);
 }
 
 }  // namespace
@@ -166,8 +155,8 @@ __device__ __forceinline__ float4 f4_zero() { return make_float4(0.f, 0.f, 0.f, 
 __device__ __forceinline__ double4 d4_zero() { return make_double4(0.0, 0.0, 0.0, 0.0); }
 
 // MINB: minimum blocks per CU the compiler must fit (1, or 6 (5 with step noise or one
-// partial output) for the 256-thread shape of batched handles: at most 76 (96) registers). NOISE: the step adds the
-// pre-drawn noise term (stochastic sampler).
+// partial output) for the 256-thread shape of batched handles: at most 76 (96) registers).
+// NOISE: the step adds the pre-drawn noise term (stochastic sampler).
 // FUSED (linear network, a slide outstanding): every block first computes the slide of the last
 // sweep itself, from its partials and snapshot (the other parity's, so no block reads what this
 // launch writes); block 0 of a sample publishes it.
@@ -229,8 +218,8 @@ __global__ __launch_bounds__(COLS * ROWS, MINB) void k_picard(Dev d) {
     float* Eh = d.Eh + (size_t)n * d.T * D;
     const float* noise = NOISE ? d.noise + (size_t)n * d.T * D : nullptr;
 
-    // ---- 64-unit partial outputs of the misses (a launch of few misses): the sum of each half's in
-    // order, then the halves'. Before any other load, so that no register is held beside theirs.
+    // ---- 64-unit partial outputs of the misses (a launch of few misses): the sum of each half's
+    // in order, then the halves'. Before any other load, so that no register is held beside theirs.
     float4 e0[TPT];
 #pragma unroll
     for (int k = 0; k < TPT; ++k) e0[k] = f4_zero();
@@ -442,8 +431,8 @@ static hipError_t launch_picard_t(Dev d, hipStream_t st, hipEvent_t e0, hipEvent
     if (d.picard_blocks != picard_blocks(d.D, d.P)) return hipErrorInvalidValue;
     // Batched handles stream from HBM with many blocks per CU: a build capped at 76 registers
     // (six waves per SIMD; 96 and five with step noise or one partial output, whose registers
-    // would otherwise spill) instead of four waves (one sample: within 2% either way, and the four-wave build is kept
-    // there). With four partial outputs the register cap would spill.
+    // would otherwise spill) instead of four waves (one sample: within 2% either way, and the
+    // four-wave build is kept there). With four partial outputs the register cap would spill.
     const bool occ = d.N >= 8;
     if constexpr (LINEAR) {
         if (d.fused_linear && pending) {

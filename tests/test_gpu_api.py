@@ -342,7 +342,8 @@ def test_whole_outputs_equal_split_outputs(wl, batch, gpu_lib):
 # (latent, H, window, samples): on 256 CUs the misses of one window in items of 32 tokens x 128,
 # 256 and 512 units and 64 tokens x 512 units (whole K, half of K at H = 2048), at the most misses
 # each takes and the fewest of the next, up to the first launch of 128-token items; then launches
-# of more than one round of those, whose last items are cut to 32 or 64 tokens, or not.
+# of more than one round of those, whose last items are cut to 32 or 64 tokens, or not. The last two
+# write whole outputs of two halves (32 and 96 items over seven rounds, cut to 32 and 64 tokens).
 FINE_SHAPES = [((4, 64, 64), 1024, P, 1) for P in (1, 2, 3, 4, 5, 8, 9)] + \
               [((4, 32, 32), 512, P, 1) for P in (1, 8, 9, 16, 17, 32, 33, 64, 65)] + \
               [((4, 16, 32), 2048, P, 1) for P in (1, 4, 5, 8, 9, 16, 17, 32, 33)] + \
@@ -350,13 +351,15 @@ FINE_SHAPES = [((4, 64, 64), 1024, P, 1) for P in (1, 2, 3, 4, 5, 8, 9)] + \
               [((4, 64, 64), 1024, 33, 1), ((4, 64, 64), 1024, 38, 1), ((4, 64, 64), 1024, 39, 1),
                ((4, 64, 64), 1024, 48, 1), ((4, 64, 64), 1024, 49, 1), ((4, 64, 64), 1024, 17, 2),
                ((4, 32, 32), 512, 129, 1), ((4, 32, 32), 512, 161, 1), ((4, 32, 32), 512, 193, 1),
-               ((4, 32, 32), 2048, 33, 1), ((4, 32, 32), 2048, 41, 1), ((4, 32, 32), 2048, 49, 1)]
+               ((4, 32, 32), 2048, 33, 1), ((4, 32, 32), 2048, 41, 1), ((4, 32, 32), 2048, 49, 1),
+               ((4, 16, 32), 1024, 32, 57), ((4, 16, 32), 1024, 32, 59)]
 
 
 @pytest.mark.parametrize("latent,hidden,P,batch", FINE_SHAPES)
 def test_few_misses_equal_split_outputs(latent, hidden, P, batch, gpu_lib):
-    """Launches of few misses, and the last items of launches of several rounds, take smaller work items; the cache and the states are bit for bit
-    those of a handle held to 128-token items with split outputs. One window, one sweep."""
+    """Launches of few misses, and the last items of launches of several rounds, take smaller work
+    items; the cache and the states are bit for bit those of a handle held to 128-token items with
+    split outputs. One window, one sweep."""
     xb = torch.from_numpy(inputs.x_init_batch(latent, batch).reshape(-1)).cuda()
     res = []
     for split in (False, True):
