@@ -119,10 +119,12 @@ typedef struct {
 #define PA_FLAG_PROFILE 2u   /* time every network launch with HIP events (paraanya_kernel_times) */
 #define PA_FLAG_PROFILE_SOLVER 4u  /* with PA_FLAG_PROFILE: time the Picard and slide launches
                                       too (their events add ~7 us per sweep of stream time) */
-#define PA_FLAG_SPLIT_OUTPUTS 8u   /* test hook (patch-MLP): every network launch writes split
-                                      partial outputs that the Picard kernel sums, instead of
+#define PA_FLAG_SPLIT_OUTPUTS 8u   /* test hook (patch-MLP): every network launch takes full
+                                      128-token work items and writes their split partial
+                                      outputs, which the Picard kernel sums, instead of
                                       choosing whole outputs written straight into the cache
-                                      when they cost no extra time; the results are the same
+                                      when they cost no extra time, smaller items for few
+                                      misses and smaller last items; the results are the same
                                       bit for bit either way */
 
 typedef struct paraanya paraanya_t;
@@ -172,7 +174,7 @@ typedef struct {
     double  picard_ms_total;  /* summed durations of the drift / Picard / cache-update kernel */
     double  slide_ms_total;   /* summed durations of the residual / slide / hit-test kernel
                                  (0 for a fused handle, see paraanya_sweep: its slide runs in
-                                 the network kernel) */
+                                 the network kernel, or the Picard kernel of a linear network) */
 } pa_ktimes_t;
 
 /* ------------------------------------------------------------------ entry points */
@@ -215,8 +217,10 @@ PA_API int paraanya_set_revisit_threshold(paraanya_t* h, double threshold);
  * Picard kernel's D/64 column blocks, at most 256 KiB) runs its sweeps fused: the window
  * slide of step (6) runs at the start of the next sweep's network kernel (every block
  * computes it; one publishes it), and whenever the host reads the state (done != NULL,
- * stats, trace, read_state) a finishing slide runs first, so every call observes the same
- * state as with a separate slide kernel. */
+ * stats, trace) a finishing slide runs first, so every call observes the same state as with
+ * a separate slide kernel. So does, in the next sweep's Picard kernel, a handle of linear
+ * samples with a window of at most 64, partial sums of at most 32 KiB per sample and at most
+ * 512 column blocks in all. */
 PA_API int paraanya_sweep(paraanya_t* h, int32_t* done);
 
 /* reset, sweeps until every sample is done, then x_out (device, N x D fp32) <- state T of
@@ -363,8 +367,8 @@ PA_API int paraanya_parareal_residuals(paraanya_parareal_t* h, int32_t k, double
 /* Test hook: the boundary states U_0..U_B of the last sample, host (B+1) x D fp32. */
 PA_API int paraanya_parareal_read_boundaries(paraanya_parareal_t* h, float* U);
 
-/* Network-launch timings since the previous call (or create), as paraanya_kernel_times;
- * STATE without PA_FLAG_PROFILE. */
+/* Network-launch timings since the previous call (or create), as paraanya_kernel_times (each
+ * launch computes the hit tests of its requests too); STATE without PA_FLAG_PROFILE. */
 PA_API int paraanya_parareal_kernel_times(paraanya_parareal_t* h, pa_ktimes_t* out);
 
 /* Free the handle (synchronizes its stream first). NULL-safe. */

@@ -545,7 +545,8 @@ __global__ __launch_bounds__(kWaves * 64) void k_eps_mlp(Dev d) {
     // gather and one h1 chunk fewer per extra half, measured ~4-6%), so they are taken when
     // 15/16 x NS x the rounds of whole items do not exceed the rounds of half items spread
     // over all blocks: with one item per block when more than half of the blocks get one,
-    // and always from about 7 rounds on.
+    // and always from about 7 rounds on. (The rule weighs full rounds: it does not know that the
+    // items past the last one may be cut, below.)
     const int fine = TOK == kTokMax && d.eps_mode != nullptr ? fine_choice<H>(mpre[d.N], d.ntok, d.fine_rows, G)
                                                              : FINE_NONE;
     const bool whole = fine == FINE_NONE && d.whole_ok && NS <= 2 &&
@@ -710,7 +711,7 @@ __global__ __launch_bounds__(kWaves * 64) void k_eps_mlp(Dev d) {
         // of the next step, also across k-blocks, are read before them; the scheduling barriers
         // keep the reads there (the compiler otherwise moves each right before its use, and every
         // four MFMAs wait for a round trip to LDS). A wave's cycles per chunk with GELU work fell
-        // by 7%; the launch gains less, since with all CUs busy the clock gives (1.7 GHz): 29
+        // by 7%; the launch gains less, since with all CUs busy power sets the clock: 29
         // misses of 1024 tokens, H = 1024, 85 -> 83 us. Two steps ahead spills (15 registers).
         constexpr int STEPS = KBC * TB4;
         bf16x8 B[2][2];

@@ -32,3 +32,13 @@ def test_counter_records_are_well_formed(record):
     for src in rec["sources"]:
         assert os.path.exists(os.path.join(ROOT, src)), src
     assert "rocprofv3" in text            # the command that produced it
+    # A kernel's file and every header of csrc/ that it includes, itself or through another one.
+    seen, todo = set(), [s for s in rec["sources"] if s.endswith(".hip")]
+    while todo:
+        src = todo.pop()
+        seen.add(src)
+        for name in re.findall(r'^#include "(\w+\.h)"', open(os.path.join(ROOT, src)).read(), re.M):
+            header = os.path.join(os.path.dirname(src), name)
+            if os.path.exists(os.path.join(ROOT, header)) and header not in seen:
+                todo.append(header)
+    assert seen == set(rec["sources"])
