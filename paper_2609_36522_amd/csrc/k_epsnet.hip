@@ -713,6 +713,12 @@ __global__ __launch_bounds__(kWaves * 64) void k_eps_mlp(Dev d) {
         // four MFMAs wait for a round trip to LDS). A wave's cycles per chunk with GELU work fell
         // by 7%; the launch gains less, since with all CUs busy power sets the clock: 29
         // misses of 1024 tokens, H = 1024, 85 -> 83 us. Two steps ahead spills (15 registers).
+        // H = 1024: the MFMAs of a step start on 8 bytes, their size (one s_nop at most). Where they
+        // fall otherwise follows from the code before the loop, and half of all places cost 1%:
+        // with the loop's start moved by 4 bytes at a time, 8 x 1024 tokens take 6738 to 6759 us a
+        // sample at the odd words and 6794 to 6811 at the even ones; aligned 6976 where those take
+        // 6987 and 7051. At H = 2048 the natural place is the faster one (Parareal 6184 against
+        // 6300 us at the other, 6346 against 6369 aligned), at H = 512 either is within 0.4%.
         constexpr int STEPS = KBC * TB4;
         bf16x8 B[2][2];
         auto load_b = [&](const __bf16* h1b, int st) {
@@ -727,6 +733,7 @@ __global__ __launch_bounds__(kWaves * 64) void k_eps_mlp(Dev d) {
                 const int st = kb * TB4 + tb4;
                 if (st + 1 < STEPS) load_b(h1b, st + 1);
                 __builtin_amdgcn_sched_barrier(0);
+                if constexpr (H == 1024) asm volatile(".p2align 3");
 #pragma unroll
                 for (int j = 0; j < 2; ++j)
 #pragma unroll
